@@ -371,15 +371,19 @@ unsigned grid_of(int64_t n) { return (unsigned)((n + BLOCK - 1) / BLOCK); }
 
 #include "rtc.h"
 
-// Shared-parameter partials of the reverse sweep: one per block, or one per
-// wavefront for the UDE (whose gradient is reduced per wavefront).
+// Blocks of the UDE kernels (32 trajectories per wavefront).
+unsigned ude_grid_of(int64_t n) {
+  return (unsigned)((n + UDE_BLOCK_TRAJ - 1) / UDE_BLOCK_TRAJ);
+}
+
+// Shared-parameter partials of the reverse sweep, one per block.
 size_t partials_bytes(int sys, int64_t n, int np, int dtype) {
-  const size_t parts = (size_t)grid_of(n) * (sys == ENS_SYS_LV_UDE ? UDE_ADJ_WAVES : 1);
+  const size_t parts = sys == ENS_SYS_LV_UDE ? ude_grid_of(n) : grid_of(n);
   return align256(parts * np * elem_size(dtype));
 }
 
 int launch_forward_ude(int mode, bool ckpt, const FwdArgs& fa, hipStream_t st) {
-  const dim3 g(grid_of(fa.ivp.n)), b(BLOCK);
+  const dim3 g(ude_grid_of(fa.ivp.n)), b(64 * UDE_WAVES);
   if (mode == MODE_SOLVE)
     hipLaunchKernelGGL((ude_forward_kernel<MODE_SOLVE, false>), g, b, 0, st, fa);
   else if (mode == MODE_RECORD && !ckpt)
@@ -900,13 +904,13 @@ int adjoint_impl(const ens_problem* p, const ens_ivp* v, const ens_record* r,
   }
   hipStream_t st = (hipStream_t)stream;
   if (p->system == ENS_SYS_LV_UDE) {
-    const dim3 g(grid_of(v->n)), b(64 * UDE_ADJ_WAVES);
+    const dim3 g(ude_grid_of(v->n)), b(64 * UDE_WAVES);
     if (ckpt)
       hipLaunchKernelGGL((ude_adjoint_kernel<true>), g, b, 0, st, aa);
     else
       hipLaunchKernelGGL((ude_adjoint_kernel<false>), g, b, 0, st, aa);
     hipLaunchKernelGGL((reduce_partials_kernel<float>), dim3(UDE_NP), dim3(BLOCK), 0, st,
-                       (const float*)workspace, (int64_t)grid_of(v->n) * UDE_ADJ_WAVES, UDE_NP,
+                       (const float*)workspace, (int64_t)ude_grid_of(v->n), UDE_NP,
                        (float*)grad_params);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? ENS_OK : hip_fail(e, "adjoint launch");
