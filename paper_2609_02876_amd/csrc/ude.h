@@ -17,12 +17,15 @@
 // activations never leave registers.  Only the 2-vector output of the MLP
 // crosses between the lane halves (v_permlane32_swap).
 //
+// What bounds these kernels is instruction time.  The FP32 matrix
+// instructions do not overlap with vector instructions, neither of the same
+// wavefront nor of another on the SIMD (8 MFMA take 0.22 us, 96 FMA 0.18 us,
+// the two interleaved 0.42 us): a kernel lasts as long as both together.
 // Why 32 trajectories a wavefront and not 64 (one per lane, two column
-// blocks): the matrix instructions of one wavefront and its vector work
-// (tanh, the stage sums) hardly overlap, so a SIMD needs two wavefronts, one
-// in each; with 64 trajectories each, 2^16 trajectories are one wavefront
-// per SIMD and every smaller ensemble leaves SIMDs idle.  The work on a
-// trajectory's own scalars is done twice now, about a twentieth of the whole.
+// blocks): with 64, 2^16 trajectories are one wavefront per SIMD, whose waits
+// for LDS and memory nothing fills, and a smaller ensemble leaves SIMDs idle
+// while each wavefront does twice the work.  The work on a trajectory's own
+// scalars is done twice now, about a twentieth of the whole.
 //
 // All lanes of a wavefront must run every right-hand side together.  The
 // kernels below therefore keep finished lanes in the loop (doing zero-length
@@ -213,16 +216,20 @@ __device__ __forceinline__ v16f mfma32(float a, float b, v16f c) {
   return __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, c, 0, 0, 0);
 }
 
-// Hidden layers: h1 = tanh(W1 y + b1), h2 = tanh(W2 h1 + b2), in the
-// accumulator layout.
+// Hidden layers in the accumulator layout: h1 = tanh(W1 y + b1) ...
 template <class Wt>
-__device__ __forceinline__ void ude_hidden(const Wt& W, const float* y, v16f& h1, v16f& h2) {
+__device__ __forceinline__ void ude_layer1(const Wt& W, const float* y, v16f& h1) {
   const float x = (__lane_id() >> 5) ? y[1] : y[0];  // feature hf of trajectory c
   W.reload();
 #pragma unroll
   for (int r = 0; r < 16; ++r) h1[r] = W.b1(r);
   h1 = mfma32(W.a1(), x, h1);
   ude_tanh_layer(h1);
+}
+
+// ... and h2 = tanh(W2 h1 + b2).
+template <class Wt>
+__device__ __forceinline__ void ude_layer2(const Wt& W, const v16f& h1, v16f& h2) {
   W.reload();
 #pragma unroll
   for (int r = 0; r < 16; ++r) h2[r] = W.b2(r);
@@ -231,39 +238,75 @@ __device__ __forceinline__ void ude_hidden(const Wt& W, const float* y, v16f& h1
   ude_tanh_layer(h2);
 }
 
-// Wt: where the weights are (UdeRegW, UdeLds); p points to one.
+// f(y) = f_LV(y) + W3 h2 + b3 for this lane's trajectory, and h2.
+// Wave-uniform: every lane of the wavefront must call it.
+template <class Wt>
+__device__ __forceinline__ void ude_rhs(const Wt& W, const float* y, float* f, v16f& h2) {
+  v16f h1;
+  ude_layer1(W, y, h1);
+  ude_layer2(W, h1, h2);
+  W.reload();
+  float p0 = 0.f, p1 = 0.f;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    p0 = fmaT(W.w3(0, r), h2[r], p0);
+    p1 = fmaT(W.w3(1, r), h2[r], p1);
+  }
+  const float n0 = ude_join(p0), n1 = ude_join(p1);
+  const float xy = y[0] * y[1];
+  f[0] = (n0 + W.b3(0)) + (LV_A * y[0] - LV_B * xy);
+  f[1] = (n1 + W.b3(1)) + (LV_D * xy - LV_G * y[1]);
+}
+
+// The system on weights in registers or LDS (UdeRegW, UdeLds); p points to them.
 template <class Wt>
 struct LvUdeOn {
   static constexpr int D = 2, NP = 0, ID = 5;
-
-  // f(y) = f_LV(y) + W3 h2 + b3 for this lane's trajectory.  Wave-uniform:
-  // every lane of the wavefront must call it.
   __device__ static inline void rhs(const float* y, const float* p, float* f) {
-    const Wt& W = *reinterpret_cast<const Wt*>(p);
-    v16f h1, h2;
-    ude_hidden(W, y, h1, h2);
-    W.reload();
-    float p0 = 0.f, p1 = 0.f;
+    v16f h2;
+    ude_rhs(*reinterpret_cast<const Wt*>(p), y, f, h2);
+  }
+};
+
+// The system as the reverse sweep evaluates it: each right-hand side of a step
+// keeps its h2 for the stage's VJP, which then forms h1 alone (one matrix
+// instruction instead of 17 and half the tanh).  The 6 x 16 values a lane are
+// private memory (scratch, written and read whole lines at a time): registers
+// and LDS are full at two wavefronts per SIMD.  p points to a UdeKeep.
+struct UdeKeep {
+  const UdeLds* W;
+  float4 (*h2)[4];  // [stage][4 x 4 units]
+  int stage;        // of the next right-hand side
+};
+
+struct LvUdeSweep {
+  static constexpr int D = 2, NP = 0, ID = 5;
+  __device__ static inline void rhs(const float* y, const float* p, float* f) {
+    UdeKeep& K = *reinterpret_cast<UdeKeep*>(const_cast<float*>(p));
+    v16f h2;
+    ude_rhs(*K.W, y, f, h2);
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      p0 = fmaT(W.w3(0, r), h2[r], p0);
-      p1 = fmaT(W.w3(1, r), h2[r], p1);
-    }
-    const float n0 = ude_join(p0), n1 = ude_join(p1);
-    const float xy = y[0] * y[1];
-    f[0] = (n0 + W.b3(0)) + (LV_A * y[0] - LV_B * xy);
-    f[1] = (n1 + W.b3(1)) + (LV_D * xy - LV_G * y[1]);
+    for (int q = 0; q < 4; ++q)
+      K.h2[K.stage][q] = make_float4(h2[4 * q], h2[4 * q + 1], h2[4 * q + 2], h2[4 * q + 3]);
+    ++K.stage;
   }
 
   // gy = (df/dy)^T w; the weight gradient of w^T f is added to the lane's
-  // accumulators g.  p is the UdeLds image.  Wave-uniform.
-  __device__ static inline void vjp(const float* y, const float* p, const float* w, float* gy,
-                                    UdeGrad& g) {
-    const UdeLds& W = *reinterpret_cast<const UdeLds*>(p);
+  // accumulators g.  kept: the stage's h2.  Wave-uniform.
+  __device__ static inline void vjp(const float* y, const UdeLds& W, const float4* kept,
+                                    const float* w, float* gy, UdeGrad& g) {
     const int l = __lane_id(), hf = l >> 5, c = l & 31;
     const int wave = threadIdx.x >> 6;
     v16f h1, h2;
-    ude_hidden(W, y, h1, h2);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float4 v = kept[q];
+      h2[4 * q] = v.x;
+      h2[4 * q + 1] = v.y;
+      h2[4 * q + 2] = v.z;
+      h2[4 * q + 3] = v.w;
+    }
+    ude_layer1(W, y, h1);
     W.reload();
 
     // output layer: dW3 += w h2^T, db3 += w, delta2 = (W3^T w) (1 - h2^2)
@@ -610,7 +653,7 @@ __device__ __forceinline__ float half_sum(float v) {
 // trips add up to the wavefront's longest trajectory, replayed and reversed.
 template <bool CKPT>
 __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const AdjArgs a) {
-  using Sys = LvUdeOn<UdeLds>;
+  using Sys = LvUdeSweep;
   using Tab = Tsit5;
   using T = float;
   constexpr int D = 2, SU = Tab::SU;
@@ -630,7 +673,6 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
   __shared__ float s_Yb[SU][D][64 * UDE_WAVES];
   ude_load_weights(s_lds, (const float*)a.ivp.params);
   __syncthreads();
-  const float* p = reinterpret_cast<const float*>(&s_lds);
   const bool ok = valid && R.status[tr] == LANE_OK;
   UdeGrad g = {};
   T lam[D] = {0.f, 0.f};
@@ -662,11 +704,7 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
 
   // the stages of the step of size hh from yb, by every lane
   T k0[D], Y[SU][D], ylast[D], klast[D], ys[D];
-  auto stages_of = [&](const T* yb, double hh) {
-    Sys::rhs(yb, p, k0);
-    step_push<Sys, Tab, T, SU, true, true, false>(yb, k0, p, T(hh), Y, ylast, klast, ys,
-                                                  nullptr);
-  };
+  float4 h2[SU][4];
 
   // Reverse every trajectory's steps down to mesh point lo (at lo = 0 with
   // the saves based there).
@@ -703,7 +741,11 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
                          yb);
         }
       }
-      stages_of(yb, hh);
+      UdeKeep keep{&s_lds, h2, 0};
+      const float* p = reinterpret_cast<const float*>(&keep);
+      Sys::rhs(yb, p, k0);
+      step_push<Sys, Tab, T, SU, true, true, false>(yb, k0, p, T(hh), Y, ylast, klast, ys,
+                                                    nullptr);
       T w[D] = {T(0), T(0)};
       if (rev && side) {
         save_cotangent<T, D>(a, s, tr, ys, two_scale, w, loss);
@@ -743,7 +785,7 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
         }
 #pragma unroll
         for (int c = 0; c < D; ++c) kb[c] = T(hh) * kb[c];
-        Sys::vjp(Yj, p, kb, Ybj, g);
+        Sys::vjp(Yj, s_lds, h2[j], kb, Ybj, g);
 #pragma unroll
         for (int c = 0; c < D; ++c) {
           lin[c] = lin[c] + Ybj[c];
@@ -774,7 +816,8 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
   if constexpr (CKPT) {
     const int F = S > 0 ? (S - 1) / K : -1;  // this trajectory's last segment
     const int F_max = wave_max(F);
-    for (int f = F_max; f >= 0; --f) {
+    // (f = 0 also where no trajectory has steps: the saves at the initial state)
+    for (int f = F_max > 0 ? F_max : 0; f >= 0; --f) {
       // replay segment f: the record (h, state) of each of its steps into the
       // trajectory's scratch page (its two lanes write the same; each reads
       // what it wrote)
@@ -795,7 +838,11 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
         if (j + 1 < len) h_next = hs[j + 1];
         if (j < len) store_rec<T, D>(scr + j * RB, hh, y);
         if (j + 1 < len_max) {  // the last step's end state is not needed
-          stages_of(y, hh);
+          using Fwd = LvUdeOn<UdeLds>;
+          const float* p = reinterpret_cast<const float*>(&s_lds);
+          Fwd::rhs(y, p, k0);
+          step_push<Fwd, Tab, T, SU, false, true, false>(y, k0, p, T(hh), Y, ylast, klast, ys,
+                                                         nullptr);
           if (j + 1 < len) {
 #pragma unroll
             for (int c = 0; c < D; ++c) y[c] = ys[c];
@@ -804,7 +851,6 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
       }
       reverse_to(f * K);
     }
-    if (F_max < 0) reverse_to(0);  // no steps at all: saves at the initial state
   } else {
     reverse_to(0);
   }
