@@ -71,7 +71,9 @@ struct AdjArgs {
   void* grad_y0;          // [D][n] or null
   double* loss_out;       // [n] or null
   void* workspace;        // shared parameters: [n_blocks][NP] partials
-  void* scratch;          // checkpointed tape: [n][page_steps] step records
+  void* scratch;          // checkpointed tape: step records, per block of 256
+                          // trajectories [page_steps][chunk][trajectory]
+                          // (the UDE: [n][page_steps])
   void* contrib;          // [n_save][D][n]: each save's cotangent for its base state
                           // (dense output: [2 n_save][D][n], one per event below)
   int32_t* events;        // dense output: [2 n_save][n] mesh point of each cotangent
@@ -1417,11 +1419,14 @@ __device__ __forceinline__ int sweep_slot(const RecView& R, int64_t base, int64_
 }
 
 // CKPT: the tape holds one state per page (segment) and the step sizes; the
-// sweep first replays each segment forward into this trajectory's scratch
-// page (full step records, the same arithmetic as the record, so the same
-// bits), then walks it backward.  Replay steps and reverse steps share one
-// loop iteration so that lanes at different phases do not serialize, and the
-// lanes of a wavefront are aligned by segment (first_gap below).
+// sweep replays each segment forward into this trajectory's scratch page
+// (full step records, the same arithmetic as the record, so the same bits),
+// then walks it backward.  The lanes of a wavefront go through the segments
+// by their index from the start of the mesh, the last first, so that they
+// replay together and reverse together, each phase in a loop of its own; a
+// lane with fewer segments idles until its last one comes.  The trips of both
+// phases add up to twice the wavefront's longest trajectory whatever the step
+// counts.
 //
 // DENSE: the saves come from the continuous extension of the step holding
 // each one (dense_saves_reverse); each save's cotangent reaches both end
@@ -1439,10 +1444,12 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   const int slot_in_block = sweep_slot(a.rec, base, n);
   const int64_t tr = base + slot_in_block;
   const bool valid = tr < n;
-  // tape lines staged through LDS for records of up to 32 bytes; larger
+  // full tape: lines staged through LDS for records of up to 32 bytes; larger
   // records (their systems run at one wave per SIMD) are read directly
-  constexpr bool STAGE = CH <= 2;
+  constexpr bool STAGE = CH <= 2 && !CKPT;
   __shared__ uint4 s_rd[STAGE ? TAPE_GROUP * CH * 256 : 1];
+  // checkpointed tape: H_GROUP step sizes of each lane
+  __shared__ uint4 s_h[CKPT ? H_GROUP / 2 * 256 : 1];
   // Rosenbrock factors of d >= 6 held in LDS during the transposed solves
   // (their possible nonzeros, 52 doubles a lane for HIRES, would otherwise
   // push the reverse step past the register file into scratch); one wave
@@ -1451,29 +1458,12 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   __shared__ T s_W[W_LDS ? lu_nnz<Sys>() * 256 : 1];
   const RecView& R = a.rec;
   const bool ok = valid && R.status[tr] == LANE_OK;
-  // CKPT: lanes of a wavefront aligned by segment.  A lane's first segment
-  // (the last of its tape) holds r = (S - 1) mod K + 1 steps, its F others K
-  // each.  Each lane waits first_gap = L - r trips before replaying its first
-  // segment and as many again after reversing it; from then on all its
-  // lanes replay their K-step segments in the same trips and reverse them in
-  // the same trips, so a replay trip skips the reverse step's work for the
-  // whole wavefront.  L = r_max, the wavefront's longest first segment, when
-  // that adds no trips to the unaligned 2 S_max (2 (r_max + K F_max) =
-  // 2 S_max: the step counts do not straddle a multiple of K); else L = K
-  // when the 2 K (F_max + 1) trips that takes are at most a quarter more
-  // (half of them replay trips); else the lanes are left unaligned.  (Every
-  // lane of the wavefront is here.)
-  int first_gap = 0;
+  // CKPT: segments by index from the start of the mesh; the lane's last one
+  // and the wavefront's (every lane of the wavefront is here)
+  int F = -1, F_max = -1;
   if constexpr (CKPT) {
-    const int S0 = ok ? R.steps[tr] : 0;
-    const int r = S0 > 0 ? (S0 - 1) % K + 1 : 0;
-    const int r_max = wave_max(r);
-    const int F_max = wave_max(S0 > 0 ? (S0 - r) / K : 0);
-    const int S_max = wave_max(S0);
-    if (r_max + K * F_max <= S_max)
-      first_gap = r_max - r;
-    else if (4 * (int64_t)K * (F_max + 1) <= 5 * (int64_t)S_max)
-      first_gap = K - r;
+    if (ok && R.steps[tr] > 0) F = (R.steps[tr] - 1) / K;
+    F_max = wave_max(F);
   }
   T* gpo = (T*)a.grad_p;
   T* gyo = (T*)a.grad_y0;
@@ -1520,27 +1510,6 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   // line, so each line is fetched once although it serves TAPE_GROUP steps.
   int grp = -1;  // first slot of the staged group; -1: none
 
-  // checkpointed tape: segment replay state
-  char* scr = CKPT ? (char*)a.scratch + (int64_t)tr * K * RB : nullptr;
-  bool rebuild = false;
-  int j_rb = 0, seg_len = 0;
-  T y_rb[D];
-#pragma unroll
-  for (int c = 0; c < D; ++c) y_rb[c] = T(0);
-  // the next replay step's size, loaded one step ahead so that its latency
-  // hides behind the current step
-  double h_rb = 0.0;
-  auto start_segment = [&](int len) {
-    const char* pgp = R.pages + (int64_t)page * R.page_bytes;
-    load_state<T, D>(pgp, y_rb);
-    h_rb = ((const double*)(pgp + YB))[0];
-    rebuild = true;
-    j_rb = 0;
-    seg_len = len;
-    grp = -1;
-  };
-  if (CKPT && S > 0) start_segment(slot + 1);
-
   // the saves based at mesh point i, from the last: their cotangents into lam
   auto take_saves = [&]() {
     while (s >= 0 && sidx == i) {
@@ -1559,57 +1528,141 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   constexpr bool AT_END = Tab::ROS && Tab::SU >= 6;
   if constexpr (AT_END) take_saves();
 
-  // CKPT: a wave-uniform loop (the wavefront leaves it when no lane is
-  // live).  A lane replaying and a lane reversing then take one step each
-  // per trip; with a per-lane loop the compiler made the replay a loop of its
-  // own, and a lane reversing waited for every other lane's whole segment.
-  bool live = true;
-  int wait = first_gap;  // trips this lane idles before its next replay
-  while (true) {
-    if constexpr (CKPT) {
-      if (!__any(live)) break;
-      if (!live) continue;
-      if (wait > 0) {
-        --wait;
-        continue;
-      }
-    }
-    if constexpr (!AT_END) {
-      if (!rebuild) {
-        take_saves();
-        if (i == 0) {
-          if constexpr (CKPT) {
-            live = false;
-            continue;
-          }
-          break;
-        }
-      }
-    } else {
-      if (i == 0) {
-        if constexpr (CKPT) {
-          live = false;
-          continue;
-        }
-        break;
-      }
-    }
-
-    T yb[D];
-    double hh;
-    {
-      if (CKPT && rebuild) {
-        hh = h_rb;
-        if (j_rb + 1 < seg_len)
-          h_rb = ((const double*)(R.pages + (int64_t)page * R.page_bytes + YB))[j_rb + 1];
+  // Recompute the stages of mesh step i (size hh from yb) and reverse through
+  // them: lam becomes the cotangent of mesh point i - 1.
+  auto reverse_step = [&](T* yb, double hh) {
+    T w[D], lin[D];
 #pragma unroll
-        for (int c = 0; c < D; ++c) yb[c] = y_rb[c];
-      } else if constexpr (!STAGE) {
-        load_rec<T, D>((CKPT ? scr : R.pages + (int64_t)page * R.page_bytes) + slot * RB, hh, yb);
+    for (int c = 0; c < D; ++c) w[c] = lam[c];
+    if constexpr (W_LDS) {
+      const LdsMat<Sys, T> Wl{s_W};
+      T u[Tab::S][D], ys[D];
+      int piv[D];
+      ros_step_lds<Sys, Tab, T, Tab::SU>(yb, p, T(hh), Wl, piv, u, ys);
+      // the reverse recomputes the stage states and Jacobian terms from
+      // (y, u) rather than keeping the forward's copies live
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        opaque(yb[c]);
+#pragma unroll
+        for (int q = 0; q < Tab::SU; ++q) opaque(u[q][c]);
+      }
+      ros_step_vjp<Sys, Tab, T, LdsMat<Sys, T>>(yb, p, T(hh), Wl, piv, u, w, lin, gp);
+    } else if constexpr (Tab::ROS) {
+      T W[D * D], u[Tab::S][D], ys[D];
+      int piv[D];
+      ros_step<Sys, Tab, T, Tab::SU>(yb, p, T(hh), W, piv, u, ys);
+      ros_step_vjp<Sys, Tab, T, T[D * D]>(yb, p, T(hh), W, piv, u, w, lin, gp);
+    } else {
+      T k0[D], Y[SU][D], ylast[D], klast[D], ys[D];
+      Sys::rhs(yb, p, k0);
+      step_push<Sys, Tab, T, SU, true, true, false>(yb, k0, p, T(hh), Y, ylast, klast, ys,
+                                                    nullptr);
+      erk_step_vjp<Sys, Tab, T>(Y, p, hh, w, lin, gp);
+    }
+#pragma unroll
+    for (int c = 0; c < D; ++c) lam[c] = lin[c];
+    --i;
+    if constexpr (AT_END) take_saves();
+  };
+
+  if constexpr (CKPT) {
+    // Segment by segment, the last first: every lane of the wavefront that has
+    // segment f (len steps of it) replays it with the others, the record's
+    // arithmetic and so the same bits, and then reverses it with them; the
+    // step j is the wavefront's, and a lane takes part while j < len.  Bound by
+    // instruction issue and by the replayed records, which go through memory:
+    // chunk by chunk, step j of the block's trajectories side by side
+    // ([j][chunk][trajectory]), so that a wavefront writes and reads whole
+    // lines, without staging, each record requested a step ahead of its use.
+    // Step sizes come 16 at a time (one line) through LDS: read one by one,
+    // each would fetch its line again.
+    // (failed and absent trajectories have the first ranks of the block, so the
+    // others' index is in [0, m), m the block's trajectories)
+    const int m = n - base < 256 ? (int)(n - base) : 256;
+    uint4* scr = reinterpret_cast<uint4*>((char*)a.scratch + base * K * RB) +
+                 ((int)threadIdx.x - (256 - m));
+    for (int f = F_max; f >= 0; --f) {
+      const int len = f <= F ? slot + 1 : 0;
+      T y[D];
+      const uint4* hs = nullptr;
+      if (len > 0) {
+        const char* pgp = R.pages + (int64_t)page * R.page_bytes;
+        load_state<T, D>(pgp, y);
+        hs = reinterpret_cast<const uint4*>(__builtin_assume_aligned(pgp + YB, 16));
+      } else {
+#pragma unroll
+        for (int c = 0; c < D; ++c) y[c] = T(0);
+      }
+      int j = 0;
+      while (true) {
+        if ((j & (H_GROUP - 1)) == 0 && j < len) {
+#pragma unroll
+          for (int q = 0; q < H_GROUP / 2; ++q) s_h[q * 256 + threadIdx.x] = hs[j / 2 + q];
+        }
+        const uint4 h2 = s_h[((j & (H_GROUP - 1)) / 2) * 256 + threadIdx.x];
+        const double hh = (j & 1) ? __hiloint2double((int)h2.w, (int)h2.z)
+                                  : __hiloint2double((int)h2.y, (int)h2.x);
+        if (j < len) {
+          RecBuf<T, D> b;
+          b.h = hh;
+#pragma unroll
+          for (int c = 0; c < D; ++c) b.y[c] = y[c];
+          const uint4* src = reinterpret_cast<const uint4*>(&b);
+#pragma unroll
+          for (int q = 0; q < CH; ++q) scr[(j * CH + q) * m] = src[q];
+        }
+        if (!__any(j + 1 < len)) break;  // the last step's end state is not needed
+        if (j + 1 < len) {
+          T ys[D];
+          if constexpr (Tab::ROS) {
+            T W[D * D], u[Tab::S][D];
+            int piv[D];
+            ros_step<Sys, Tab, T, Tab::SU>(y, p, T(hh), W, piv, u, ys);
+          } else {
+            T k0[D], Y[SU][D], ylast[D], klast[D];
+            Sys::rhs(y, p, k0);
+            step_push<Sys, Tab, T, SU, false, true, false>(y, k0, p, T(hh), Y, ylast, klast, ys,
+                                                           nullptr);
+          }
+#pragma unroll
+          for (int c = 0; c < D; ++c) y[c] = ys[c];
+        }
+        ++j;
+      }
+      RecBuf<T, D> ahead;
+      auto fetch = [&](int jj) {
+        uint4* dst = reinterpret_cast<uint4*>(&ahead);
+#pragma unroll
+        for (int q = 0; q < CH; ++q) dst[q] = scr[(jj * CH + q) * m];
+      };
+      if (j < len) fetch(j);
+      for (; j >= 0; --j) {
+        RecBuf<T, D> b = ahead;
+        if (j > 0 && j - 1 < len) fetch(j - 1);
+        if (j < len) {
+          if constexpr (!AT_END) take_saves();
+          reverse_step(b.y, b.h);
+        }
+      }
+      if (len > 0 && f > 0) {
+        page = prev_page(R, page);
+        slot = K - 1;
+      }
+    }
+    if constexpr (!AT_END) take_saves();  // the saves at the initial state
+  } else {
+    while (true) {
+      if constexpr (!AT_END) take_saves();
+      if (i == 0) break;
+      T yb[D];
+      double hh;
+      if constexpr (!STAGE) {
+        load_rec<T, D>(R.pages + (int64_t)page * R.page_bytes + slot * RB, hh, yb);
       } else {
         const int g0 = slot & ~(TAPE_GROUP - 1);
         if (g0 != grp) {
-          const char* base = CKPT ? scr : R.pages + (int64_t)page * R.page_bytes;
+          const char* base = R.pages + (int64_t)page * R.page_bytes;
           const uint4* src = reinterpret_cast<const uint4*>(
               __builtin_assume_aligned(base + g0 * RB, 16));
 #pragma unroll
@@ -1624,80 +1677,11 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
 #pragma unroll
         for (int c = 0; c < D; ++c) yb[c] = b.y[c];
       }
-    }
-
-    // recompute the stages of this step
-    constexpr int NW = Tab::ROS ? D * D : 1;
-    constexpr int NU = Tab::ROS ? Tab::S : 1;
-    constexpr int NY = Tab::ROS ? 1 : SU;
-    T W[NW], u[NU][D];
-    int piv[D];
-    T Y[NY][D], ys[D];
-    if constexpr (W_LDS) {
-      ros_step_lds<Sys, Tab, T, Tab::SU>(yb, p, T(hh), LdsMat<Sys, T>{s_W}, piv, u, ys);
-    } else if constexpr (Tab::ROS) {
-      ros_step<Sys, Tab, T, Tab::SU>(yb, p, T(hh), W, piv, u, ys);
-    } else {
-      T k0[D], ylast[D], klast[D];
-      Sys::rhs(yb, p, k0);
-      step_push<Sys, Tab, T, SU, true, true, false>(yb, k0, p, T(hh), Y, ylast, klast, ys,
-                                                    nullptr);
-    }
-    if (CKPT && rebuild) {
-      // one replay step of the segment: keep its record, move on.  Records
-      // of up to 32 bytes wait in this lane's group slots (free while it
-      // replays) and go out a whole group (one cache line) at a time; the
-      // segment's last group stays there for the reverse steps that follow.
-      if constexpr (STAGE) {
-        const int q = j_rb & (TAPE_GROUP - 1);
-        stage_rec<T, D>(s_rd, q * CH, hh, yb);
-        if (q == TAPE_GROUP - 1 || j_rb + 1 == seg_len) {
-          flush_recs<T, D>(s_rd, q + 1, scr + (j_rb - q) * RB);
-          if (j_rb + 1 == seg_len) grp = j_rb - q;
-        }
-      } else {
-        store_rec<T, D>(scr + j_rb * RB, hh, yb);
-      }
-#pragma unroll
-      for (int c = 0; c < D; ++c) y_rb[c] = ys[c];
-      if (++j_rb == seg_len) rebuild = false;
-      continue;
-    }
-    T w[D];
-#pragma unroll
-    for (int c = 0; c < D; ++c) w[c] = lam[c];
-
-    // reverse through the stages: kbar_j = h (b_j w + sum_{l>j} a_lj Ybar_l)
-    T lin[D];
-    if constexpr (W_LDS) {
-      const LdsMat<Sys, T> Wl{s_W};
-      // the reverse recomputes the stage states and Jacobian terms from
-      // (y, u) rather than keeping the forward's copies live
-#pragma unroll
-      for (int c = 0; c < D; ++c) {
-        opaque(yb[c]);
-#pragma unroll
-        for (int q = 0; q < (Tab::ROS ? Tab::SU : 0); ++q) opaque(u[q][c]);
-      }
-      ros_step_vjp<Sys, Tab, T, LdsMat<Sys, T>>(yb, p, T(hh), Wl, piv, u, w, lin, gp);
-    } else if constexpr (Tab::ROS) {
-      ros_step_vjp<Sys, Tab, T, T[NW]>(yb, p, T(hh), W, piv, u, w, lin, gp);
-    } else {
-      erk_step_vjp<Sys, Tab, T>(Y, p, hh, w, lin, gp);
-    }
-
-#pragma unroll
-    for (int c = 0; c < D; ++c) lam[c] = lin[c];
-    --i;
-    if constexpr (AT_END) take_saves();
-    if (--slot < 0 && i > 0) {
-      page = prev_page(R, page);
-      slot = K - 1;
-      grp = -1;
-      if (CKPT) {
-        start_segment(K);
-        wait = first_gap;
-        first_gap = 0;
+      reverse_step(yb, hh);
+      if (--slot < 0 && i > 0) {
+        page = prev_page(R, page);
+        slot = PAGE_STEPS - 1;
+        grp = -1;
       }
     }
   }
@@ -1841,15 +1825,15 @@ __global__ void __launch_bounds__(256) dense_saves_kernel(const FwdArgs a) {
 // Blocks per CU the compiler is asked to fit in the reverse sweep: 3 for the
 // FP64 Lorenz / Tsit5 sweep, which then lands at 124 registers with no
 // spill (4 waves per SIMD); asking for 4 gives the same occupancy with a
-// spill.  No request for the others.
-template <class Sys, class Tab, class T>
+// spill.  With a checkpointed tape it would land at 129, so 4.  No request for the others.
+template <class Sys, class Tab, class T, bool CKPT>
 struct AdjBlocks {
   static constexpr int value =
-      (Sys::ID == 1 && Tab::ORDER == 5 && !Tab::ROS && sizeof(T) == 8) ? 3 : 1;
+      (Sys::ID == 1 && Tab::ORDER == 5 && !Tab::ROS && sizeof(T) == 8) ? (CKPT ? 4 : 3) : 1;
 };
 
 template <class Sys, class Tab, class T, bool SHARED, bool CKPT, bool DENSE = false>
-__global__ void __launch_bounds__(256, (AdjBlocks<Sys, Tab, T>::value))
+__global__ void __launch_bounds__(256, (AdjBlocks<Sys, Tab, T, CKPT>::value))
     erk_adjoint_kernel(const AdjArgs a) {
   erk_adjoint_body<Sys, Tab, T, SHARED, CKPT, DENSE>(a, blockIdx.x);
 }
