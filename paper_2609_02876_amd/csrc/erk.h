@@ -1508,7 +1508,6 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   // Tape reads: the TAPE_GROUP records of a 128-byte line are loaded into
   // LDS together (chunk-major, as in the record) when the sweep enters the
   // line, so each line is fetched once although it serves TAPE_GROUP steps.
-  int grp = -1;  // first slot of the staged group; -1: none
 
   // the saves based at mesh point i, from the last: their cotangents into lam
   auto take_saves = [&]() {
@@ -1652,38 +1651,37 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
     }
     if constexpr (!AT_END) take_saves();  // the saves at the initial state
   } else {
-    while (true) {
-      if constexpr (!AT_END) take_saves();
-      if (i == 0) break;
-      T yb[D];
-      double hh;
-      if constexpr (!STAGE) {
-        load_rec<T, D>(R.pages + (int64_t)page * R.page_bytes + slot * RB, hh, yb);
-      } else {
-        const int g0 = slot & ~(TAPE_GROUP - 1);
-        if (g0 != grp) {
-          const char* base = R.pages + (int64_t)page * R.page_bytes;
-          const uint4* src = reinterpret_cast<const uint4*>(
-              __builtin_assume_aligned(base + g0 * RB, 16));
+    // Full tape, a group of TAPE_GROUP steps (for 32-byte records one line) at
+    // a time.  A lane's first group (the last of its tape) may be shorter; at
+    // the end of the inner loop it waits for the wavefront's others, so from
+    // then on all lanes fetch their groups in the same trips.
+    while (i > 0) {
+      const char* pgp = R.pages + (int64_t)page * R.page_bytes;
+      const int g0 = slot & ~(TAPE_GROUP - 1);
+      if constexpr (STAGE) {
+        const uint4* src = reinterpret_cast<const uint4*>(
+            __builtin_assume_aligned(pgp + g0 * RB, 16));
 #pragma unroll
-          for (int q = 0; q < TAPE_GROUP * CH; ++q) s_rd[q * 256 + threadIdx.x] = src[q];
-          grp = g0;
-        }
-        RecBuf<T, D> b;
-        uint4* dst = reinterpret_cast<uint4*>(&b);
-#pragma unroll
-        for (int q = 0; q < CH; ++q) dst[q] = s_rd[((slot - g0) * CH + q) * 256 + threadIdx.x];
-        hh = b.h;
-#pragma unroll
-        for (int c = 0; c < D; ++c) yb[c] = b.y[c];
+        for (int q = 0; q < TAPE_GROUP * CH; ++q) s_rd[q * 256 + threadIdx.x] = src[q];
       }
-      reverse_step(yb, hh);
-      if (--slot < 0 && i > 0) {
+      for (; slot >= g0; --slot) {
+        if constexpr (!AT_END) take_saves();
+        RecBuf<T, D> b;
+        if constexpr (STAGE) {
+          uint4* dst = reinterpret_cast<uint4*>(&b);
+#pragma unroll
+          for (int q = 0; q < CH; ++q) dst[q] = s_rd[((slot - g0) * CH + q) * 256 + threadIdx.x];
+        } else {
+          load_rec<T, D>(pgp + slot * RB, b.h, b.y);
+        }
+        reverse_step(b.y, b.h);
+      }
+      if (slot < 0 && i > 0) {
         page = prev_page(R, page);
         slot = PAGE_STEPS - 1;
-        grp = -1;
       }
     }
+    if constexpr (!AT_END) take_saves();
   }
 
   if (a.loss_kind != LOSS_COTANGENT) loss = a.scale * loss;
