@@ -869,18 +869,13 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
       // a side step onto the base point itself is the identity (1/(gamma h)
       // would divide by zero): evaluate at a harmless h and keep y
       const bool zero = (hh == 0.0);
-      T W[D * D], u[Tab::S][D];
-      int piv[D];
+      T e[D];
       // a replay on a given mesh forms only the stages that enter y_new
-      ros_step<Sys, Tab, T, (MODE == MODE_FROZEN ? Tab::SU : Tab::S)>(
-          y, p, T(zero ? 1.0 : hh), W, piv, u, ynew);
+      ros_eval<Sys, Tab, T, (MODE == MODE_FROZEN ? Tab::SU : Tab::S), MODE != MODE_FROZEN>(
+          y, p, T(zero ? 1.0 : hh), ynew, e);
 #pragma unroll
       for (int c = 0; c < D; ++c) ynew[c] = zero ? y[c] : ynew[c];
-      if constexpr (MODE != MODE_FROZEN) {
-        T e[D];
-        ros_errvec<Tab, D, T>(u, e);
-        err = ros_ms<D, T>(y, ynew, e, rtol, atol);
-      }
+      if constexpr (MODE != MODE_FROZEN) err = ros_ms<D, T>(y, ynew, e, rtol, atol);
     } else {
       T kb[D];
       if constexpr (Tab::FSAL) {
@@ -1223,38 +1218,16 @@ __device__ __forceinline__ void erk_step_vjp(const T (&Y)[Tab::SU][Sys::D], cons
 
 // A save step of size hh != 0 from its base state yb: recompute it, form
 // the save's cotangent from the state it reaches (cot(ys, w)), and reverse
-// it: lin = d(ys)/dyb^T w, g += d(ys)/dp^T w.  Rosenbrock factors of d >= 6
-// go through the lane's LDS slots sW, as in the sweep's loop.
-template <class Sys, class Tab, class T, bool W_LDS, class Cot>
-__device__ __forceinline__ void save_step_reverse(const T* yb, const T* p, double hh, T* sW,
-                                                  Cot&& cot, T* lin, T* g) {
+// it: lin = d(ys)/dyb^T w, g += d(ys)/dp^T w.  Rosenbrock increments of
+// d >= 6 go through the lane's LDS slots sU, as in the sweep's loop.
+template <class Sys, class Tab, class T, bool U_LDS, class Cot>
+__device__ __forceinline__ void save_step_reverse(const T* yb, const T* p, double hh, T* sU,
+                                                  Cot& cot, T* lin, T* g) {
   constexpr int D = Sys::D;
-  T ys[D], w[D];
   if constexpr (Tab::ROS) {
-    T u[Tab::S][D];
-    int piv[D];
-    if constexpr (W_LDS) {
-      ros_step_lds<Sys, Tab, T, Tab::SU>(yb, p, T(hh), LdsMat<Sys, T>{sW}, piv, u, ys);
-    } else {
-      T W[D * D];
-      ros_step<Sys, Tab, T, Tab::SU>(yb, p, T(hh), W, piv, u, ys);
-      cot(ys, w);
-      ros_step_vjp<Sys, Tab, T, T[D * D]>(yb, p, T(hh), W, piv, u, w, lin, g);
-      return;
-    }
-    cot(ys, w);
-    T ybo[D];
-#pragma unroll
-    for (int c = 0; c < D; ++c) {
-      ybo[c] = yb[c];
-      opaque(ybo[c]);
-#pragma unroll
-      for (int q = 0; q < Tab::SU; ++q) opaque(u[q][c]);
-    }
-    ros_step_vjp<Sys, Tab, T, LdsMat<Sys, T>>(ybo, p, T(hh), LdsMat<Sys, T>{sW}, piv, u, w, lin,
-                                              g);
+    ros_reverse<Sys, Tab, T, U_LDS>(yb, p, T(hh), sU, cot, lin, g);
   } else {
-    T k0[D], Y[Tab::SU][D], ylast[D], klast[D];
+    T ys[D], w[D], k0[D], Y[Tab::SU][D], ylast[D], klast[D];
     Sys::rhs(yb, p, k0);
     step_push<Sys, Tab, T, Tab::SU, true, true, false>(yb, k0, p, T(hh), Y, ylast, klast, ys,
                                                        nullptr);
@@ -1269,9 +1242,9 @@ __device__ __forceinline__ void save_step_reverse(const T* yb, const T* p, doubl
 // reverse of its side step from the recorded base state, with the parameter
 // terms added into g.  The cotangent each save gives its base state goes to
 // a.contrib.
-template <class Sys, class Tab, class T, bool W_LDS>
+template <class Sys, class Tab, class T, bool U_LDS>
 __device__ __forceinline__ void save_steps_reverse(const AdjArgs& a, int64_t tr, const T* p,
-                                                   T two_scale, T* sW, T* g, double& loss) {
+                                                   T two_scale, T* sU, T* g, double& loss) {
   constexpr int D = Sys::D;
   const RecView& R = a.rec;
   const int64_t n = a.ivp.n;
@@ -1288,7 +1261,7 @@ __device__ __forceinline__ void save_steps_reverse(const AdjArgs& a, int64_t tr,
       auto cot = [&](const T* ys, T* w) {
         save_cotangent<T, D>(a, ss, tr, ys, two_scale, w, loss);
       };
-      save_step_reverse<Sys, Tab, T, W_LDS>(yb, p, dt, sW, cot, cs, g);
+      save_step_reverse<Sys, Tab, T, U_LDS>(yb, p, dt, sU, cot, cs, g);
     }
 #pragma unroll
     for (int c = 0; c < D; ++c) cb[((int64_t)ss * D + c) * n + tr] = cs[c];
@@ -1448,14 +1421,13 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   // records (their systems run at one wave per SIMD) are read directly
   constexpr bool STAGE = CH <= 2 && !CKPT;
   __shared__ uint4 s_rd[STAGE ? TAPE_GROUP * CH * 256 : 1];
-  // checkpointed tape: H_GROUP step sizes of each lane
+  // Rodas4 steps of d >= 6: the increments wait in LDS for the reverse (98 KB a
+  // block for HIRES, one wave per SIMD either way; Rosenbrock23's two stay in
+  // registers)
+  constexpr bool U_LDS = Tab::ROS && D >= 6 && Tab::SU >= 4;
+  __shared__ T s_U[U_LDS ? Tab::SU * D * 256 : 1];
+  // checkpointed tape: the next H_GROUP step sizes of each lane
   __shared__ uint4 s_h[CKPT ? H_GROUP / 2 * 256 : 1];
-  // Rosenbrock factors of d >= 6 held in LDS during the transposed solves
-  // (their possible nonzeros, 52 doubles a lane for HIRES, would otherwise
-  // push the reverse step past the register file into scratch); one wave
-  // per SIMD either way
-  constexpr bool W_LDS = Tab::ROS && D >= 6;
-  __shared__ T s_W[W_LDS ? lu_nnz<Sys>() * 256 : 1];
   const RecView& R = a.rec;
   const bool ok = valid && R.status[tr] == LANE_OK;
   // CKPT: segments by index from the start of the mesh; the lane's last one
@@ -1486,7 +1458,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   if constexpr (DENSE)
     dense_saves_reverse<Sys, T>(a, tr, p, two_scale, gp, loss);
   else
-    save_steps_reverse<Sys, Tab, T, W_LDS>(a, tr, p, two_scale, s_W, gp, loss);
+    save_steps_reverse<Sys, Tab, T, U_LDS>(a, tr, p, two_scale, s_U, gp, loss);
 
   // Save bookkeeping, walked from the last save to the first: the save's
   // base index and its cotangent in a.contrib.
@@ -1533,25 +1505,12 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
     T w[D], lin[D];
 #pragma unroll
     for (int c = 0; c < D; ++c) w[c] = lam[c];
-    if constexpr (W_LDS) {
-      const LdsMat<Sys, T> Wl{s_W};
-      T u[Tab::S][D], ys[D];
-      int piv[D];
-      ros_step_lds<Sys, Tab, T, Tab::SU>(yb, p, T(hh), Wl, piv, u, ys);
-      // the reverse recomputes the stage states and Jacobian terms from
-      // (y, u) rather than keeping the forward's copies live
+    if constexpr (Tab::ROS) {
+      auto cot = [&](const T*, T* v) {
 #pragma unroll
-      for (int c = 0; c < D; ++c) {
-        opaque(yb[c]);
-#pragma unroll
-        for (int q = 0; q < Tab::SU; ++q) opaque(u[q][c]);
-      }
-      ros_step_vjp<Sys, Tab, T, LdsMat<Sys, T>>(yb, p, T(hh), Wl, piv, u, w, lin, gp);
-    } else if constexpr (Tab::ROS) {
-      T W[D * D], u[Tab::S][D], ys[D];
-      int piv[D];
-      ros_step<Sys, Tab, T, Tab::SU>(yb, p, T(hh), W, piv, u, ys);
-      ros_step_vjp<Sys, Tab, T, T[D * D]>(yb, p, T(hh), W, piv, u, w, lin, gp);
+        for (int c = 0; c < D; ++c) v[c] = w[c];
+      };
+      ros_reverse<Sys, Tab, T, U_LDS>(yb, p, T(hh), s_U, cot, lin, gp);
     } else {
       T k0[D], Y[SU][D], ylast[D], klast[D], ys[D];
       Sys::rhs(yb, p, k0);
@@ -1615,9 +1574,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
         if (j + 1 < len) {
           T ys[D];
           if constexpr (Tab::ROS) {
-            T W[D * D], u[Tab::S][D];
-            int piv[D];
-            ros_step<Sys, Tab, T, Tab::SU>(y, p, T(hh), W, piv, u, ys);
+            ros_eval<Sys, Tab, T, Tab::SU, false>(y, p, T(hh), ys, nullptr);
           } else {
             T k0[D], Y[SU][D], ylast[D], klast[D];
             Sys::rhs(y, p, k0);
@@ -1722,11 +1679,17 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
 
 // Blocks per CU the compiler is asked to fit in the record of the FP64
 // Lorenz / Tsit5 ensemble (4: four waves per SIMD; five need a 96-register
-// budget that spills and runs 50 % slower); no request otherwise.
+// budget that spills and runs 50 % slower) and of the built-in Rosenbrock
+// systems of d < 6 (4: what the path without interchanges needs; the general
+// one, which they hardly take, spills a little).  No request otherwise: at two
+// waves per SIMD HIRES's path without interchanges runs 10 % faster, but the
+// general one spills some 640 B a lane and takes eight times as long.
 template <class Sys, class Tab, class T>
 struct FwdBlocks {
   static constexpr int value =
-      (Sys::ID == 1 && Tab::ORDER == 5 && !Tab::ROS && sizeof(T) == 8) ? 4 : 1;
+      (Sys::ID == 1 && Tab::ORDER == 5 && !Tab::ROS && sizeof(T) == 8) ? 4
+      : (Tab::ROS && Sys::D < 6 && Sys::ID < 1000)                     ? 4
+                                                                       : 1;
 };
 
 template <class Sys, class Tab, class T, int MODE, bool CKPT, bool DENSE = false>
@@ -1823,11 +1786,16 @@ __global__ void __launch_bounds__(256) dense_saves_kernel(const FwdArgs a) {
 // Blocks per CU the compiler is asked to fit in the reverse sweep: 3 for the
 // FP64 Lorenz / Tsit5 sweep, which then lands at 124 registers with no
 // spill (4 waves per SIMD); asking for 4 gives the same occupancy with a
-// spill.  With a checkpointed tape it would land at 129, so 4.  No request for the others.
+// spill.  With a checkpointed tape it would land at 129, so 4.
+// The built-in Rosenbrock systems of d < 6 as their records, short of a spill
+// in the path without interchanges (a reload waits behind the tape's loads).
+// No request for the others.
 template <class Sys, class Tab, class T, bool CKPT>
 struct AdjBlocks {
   static constexpr int value =
-      (Sys::ID == 1 && Tab::ORDER == 5 && !Tab::ROS && sizeof(T) == 8) ? (CKPT ? 4 : 3) : 1;
+      (Sys::ID == 1 && Tab::ORDER == 5 && !Tab::ROS && sizeof(T) == 8) ? (CKPT ? 4 : 3)
+      : (Tab::ROS && Sys::D < 6 && Sys::ID < 1000) ? (Tab::SU >= 4 ? 2 : 3)
+                                                   : 1;
 };
 
 template <class Sys, class Tab, class T, bool SHARED, bool CKPT, bool DENSE = false>

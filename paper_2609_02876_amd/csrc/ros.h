@@ -45,7 +45,9 @@ constexpr unsigned jac_row_of(int, long) {
 // below k with a possibly nonzero column-k entry are the pivot candidates;
 // the interchange may give row k any candidate's pattern and a candidate
 // row k's; then each row below k with a possibly nonzero column-k entry is
-// eliminated, taking on the pivot row's pattern right of column k.
+// eliminated, taking on the pivot row's pattern right of column k.  PIV
+// false: the pattern where nothing is interchanged (row k is the only
+// candidate of column k).
 template <int D>
 struct LuPattern {
   unsigned cand[D];    // step k: candidate pivot rows (bit i), row k included
@@ -53,11 +55,9 @@ struct LuPattern {
   unsigned pivrow[D];  // step k: the pivot row's pattern after the interchange
   unsigned elim[D];    // step k: rows below k that are eliminated
   unsigned fin[D];     // the factors: L below the diagonal, U and 1/U_kk on and above
-  int slot[D * D];     // entry -> its place among the factors' possible nonzeros (-1: zero)
-  int nnz;             // number of those
 };
 
-template <class Sys>
+template <class Sys, bool PIV = true>
 constexpr LuPattern<Sys::D> lu_pattern() {
   constexpr int D = Sys::D;
   LuPattern<D> P{};
@@ -67,7 +67,7 @@ constexpr LuPattern<Sys::D> lu_pattern() {
     for (int i = 0; i < D; ++i) P.before[k][i] = M[i];
     unsigned cand = 1u << k, any = M[k];
     for (int i = k + 1; i < D; ++i)
-      if ((M[i] >> k) & 1u) {
+      if (PIV && ((M[i] >> k) & 1u)) {
         cand |= 1u << i;
         any |= M[i];
       }
@@ -86,12 +86,7 @@ constexpr LuPattern<Sys::D> lu_pattern() {
       }
     P.elim[k] = el;
   }
-  int nz = 0;
-  for (int i = 0; i < D; ++i) {
-    P.fin[i] = M[i];
-    for (int j = 0; j < D; ++j) P.slot[i * D + j] = ((M[i] >> j) & 1u) ? nz++ : -1;
-  }
-  P.nnz = nz;
+  for (int i = 0; i < D; ++i) P.fin[i] = M[i];
   return P;
 }
 
@@ -152,6 +147,58 @@ __device__ __forceinline__ void ros_factor(const T* y, const T* p, T h, T (&W)[S
   }
 }
 
+// The factorisation where every column's pivot is on the diagonal: the same
+// operations as ros_factor's on a lane that interchanges nothing (what that
+// does on the fill of other pivot orders adds exact zeros).  Returns whether
+// the lane would have interchanged rows, in which case the factors are not
+// ros_factor's.
+template <class Sys, class Tab, class T>
+__device__ __forceinline__ bool ros_factor_plain(const T* y, const T* p, T h,
+                                                 T (&W)[Sys::D * Sys::D]) {
+  constexpr int D = Sys::D;
+  constexpr LuPattern<D> P = lu_pattern<Sys, false>();
+  Sys::jac(y, p, W);
+  const T dg = T(1.0) / (T(Tab::GAMMA) * h);
+#pragma unroll
+  for (int i = 0; i < D * D; ++i) W[i] = -W[i];
+#pragma unroll
+  for (int i = 0; i < D; ++i) W[i * D + i] = W[i * D + i] + dg;
+  bool sw = false;
+#pragma unroll
+  for (int k = 0; k < D; ++k) {
+    const T best = fabs(W[k * D + k]);
+    const T r = T(1.0) / W[k * D + k];
+    W[k * D + k] = r;
+#pragma unroll
+    for (int i = k + 1; i < D; ++i) {
+      if (!has(P.elim[k], i)) continue;  // its multiplier is zero
+      sw |= fabs(W[i * D + k]) > best;
+      const T l = W[i * D + k] * r;
+      W[i * D + k] = l;
+#pragma unroll
+      for (int j = k + 1; j < D; ++j)
+        if (has(P.pivrow[k], j)) W[i * D + j] = fmaT(-l, W[k * D + j], W[i * D + j]);
+    }
+  }
+  return sw;
+}
+
+// The factors of ros_factor_plain: indexed as the register array they are in;
+// the solves take them without interchanges and with the smaller pattern.
+template <class Sys, class T>
+struct PlainMat {
+  T w[Sys::D * Sys::D];
+  __device__ __forceinline__ T operator[](int e) const { return w[e]; }
+};
+template <class Mat>
+struct Pivoted {
+  static constexpr bool value = true;
+};
+template <class Sys, class T>
+struct Pivoted<PlainMat<Sys, T>> {
+  static constexpr bool value = false;
+};
+
 // Apply the interchanges of the factorisation to v, first to last (only
 // the candidate rows of each step can have been interchanged).
 template <class Sys, class T>
@@ -189,79 +236,13 @@ __device__ __forceinline__ void permute_bwd(const int (&piv)[Sys::D], T* v) {
   }
 }
 
-// The factors of one lane held in LDS, only the entries that can be
-// nonzero: entry e at base[slot(e) * 256 + lane] (consecutive lanes on
-// consecutive words, so a wave's access is one conflict-free sweep).
-// Indexing as for a register array; an entry that is always zero is never
-// read.
-template <class Sys, class T>
-struct LdsMat {
-  T* base;
-  __device__ __forceinline__ T operator[](int e) const {
-    constexpr LuPattern<Sys::D> P = lu_pattern<Sys>();
-    return base[P.slot[e] * 256 + threadIdx.x];
-  }
-};
-
-// LDS words a lane's factors take.
-template <class Sys>
-constexpr int lu_nnz() {
-  return lu_pattern<Sys>().nnz;
-}
-
-// Before each solve from LDS: a compiler memory barrier, so that every solve
-// reads the factors afresh instead of the compiler merging the reads of
-// successive solves (which would keep all the factors in registers).
-template <class Sys, class T>
-__device__ __forceinline__ void reload_point(const LdsMat<Sys, T>&) {
-  __asm__ __volatile__("" ::: "memory");
-}
-template <class A>
-__device__ __forceinline__ void reload_point(const A&) {}
-
-
-// After a solve from LDS: its result is taken as new (an optimisation
-// barrier per component), which keeps the compiler from interleaving the
-// arithmetic of successive solves; without it the 8 x 8 reverse step holds
-// too much at once and spills about 2 KB a lane.
-template <class Sys, class T>
-__device__ __forceinline__ void solved_point(const LdsMat<Sys, T>&, T* x) {
-#pragma unroll
-  for (int c = 0; c < Sys::D; ++c) __asm__ __volatile__("" : "+v"(x[c]));
-}
-template <class Sys, class T, class A>
-__device__ __forceinline__ void solved_point(const A&, T*) {}
-
-// An optimisation barrier on a value: the compiler must treat x as changed,
-// so expressions of it formed afterwards are computed afresh instead of
-// reusing (and keeping alive) equal ones formed before.  No instruction.
-template <class T>
-__device__ __forceinline__ void opaque(T& x) {
-  __asm__ __volatile__("" : "+v"(x));
-}
-
-// Copy register factors into a lane's LDS slots (the entries that can be
-// nonzero).  The empty asm with a memory clobber keeps the compiler from
-// forwarding the stored values to the later reads, which would keep the
-// factors live in registers after all.
-template <class Sys, class T>
-__device__ __forceinline__ void put_lds(const T (&W)[Sys::D * Sys::D], const LdsMat<Sys, T>& M) {
-  constexpr int D = Sys::D;
-  constexpr LuPattern<D> P = lu_pattern<Sys>();
-#pragma unroll
-  for (int e = 0; e < D * D; ++e)
-    if (P.slot[e] >= 0) M.base[P.slot[e] * 256 + threadIdx.x] = W[e];
-  __asm__ __volatile__("" ::: "memory");
-}
-
 // x = W^{-1} b in place: L z = P b forward, then U x = z backward (the
 // diagonal holds 1/U_kk); the zeros of L and U skipped.
 template <class Sys, class T, class Mat>
 __device__ __forceinline__ void lu_solve(const Mat& W, const int (&piv)[Sys::D], T* x) {
   constexpr int D = Sys::D;
-  constexpr LuPattern<D> P = lu_pattern<Sys>();
-  reload_point(W);
-  permute_fwd<Sys, T>(piv, x);
+  constexpr LuPattern<D> P = lu_pattern<Sys, Pivoted<Mat>::value>();
+  if constexpr (Pivoted<Mat>::value) permute_fwd<Sys, T>(piv, x);
 #pragma unroll
   for (int i = 0; i < D; ++i) {
     T acc = x[i];
@@ -281,12 +262,11 @@ __device__ __forceinline__ void lu_solve(const Mat& W, const int (&piv)[Sys::D],
 }
 
 // z = W^{-T} b in place: U^T v = b forward, L^T w = v backward, z = P^T w.
-// W: the factors as a register array or an LdsMat.
+// W: the factors (a register array, or a PlainMat).
 template <class Sys, class T, class Mat>
 __device__ __forceinline__ void lu_solve_t(const Mat& W, const int (&piv)[Sys::D], T* z) {
   constexpr int D = Sys::D;
-  constexpr LuPattern<D> P = lu_pattern<Sys>();
-  reload_point(W);
+  constexpr LuPattern<D> P = lu_pattern<Sys, Pivoted<Mat>::value>();
 #pragma unroll
   for (int i = 0; i < D; ++i) {
     T acc = z[i];
@@ -303,7 +283,7 @@ __device__ __forceinline__ void lu_solve_t(const Mat& W, const int (&piv)[Sys::D
       if (has(P.fin[j], i)) acc = fmaT(-W[j * D + i], z[j], acc);
     z[i] = acc;
   }
-  permute_bwd<Sys, T>(piv, z);
+  if constexpr (Pivoted<Mat>::value) permute_bwd<Sys, T>(piv, z);
 }
 
 // Stage input Y_i = y + sum_{j<i} A_ij u_j (index order, first term a
@@ -329,7 +309,7 @@ __device__ __forceinline__ void ros_input(int i, const T* y, const T (&u)[Tab::S
 // factors left in W/piv for the reverse, and y_new: Y_s + u_s, or the last
 // stage input Y_s (NEW_AT_INPUT).  NSC = S forms every stage (a trial step
 // needs the last for its error estimate); NSC = SU only those that enter
-// y_new (a replay).  W: the factors as a register array or an LdsMat.
+// y_new (a replay).  W: the factors (a register array, or a PlainMat).
 template <class Sys, class Tab, class T, class Mat, int NSC = Tab::S>
 __device__ __forceinline__ void ros_stages(const T* y, const T* p, T h, const Mat& W,
                                            const int (&piv)[Sys::D], T (&u)[Tab::S][Sys::D],
@@ -358,7 +338,6 @@ __device__ __forceinline__ void ros_stages(const T* y, const T* p, T h, const Ma
       u[i][c] = first ? F[c] : fmah(acc, hinv, F[c]);
     }
     lu_solve<Sys, T, Mat>(W, piv, u[i]);
-    solved_point<Sys, T>(W, u[i]);
   }
   if constexpr (Tab::NEW_AT_INPUT) {
     ros_input<Tab, D, T>(NS - 1, y, u, ynew);
@@ -393,19 +372,53 @@ __device__ __forceinline__ void ros_errvec(const T (&u)[Tab::S][D], T* e) {
   }
 }
 
-// The same step with the factors moved to this lane's LDS slots right after
-// the factorisation (the same values, so the same results), for systems
-// whose factors crowd the registers of the reverse sweep.
-template <class Sys, class Tab, class T, int NSC = Tab::S>
-__device__ __forceinline__ void ros_step_lds(const T* y, const T* p, T h,
-                                             const LdsMat<Sys, T>& Wl,
-                                             int (&piv)[Sys::D], T (&u)[Tab::S][Sys::D],
-                                             T* ynew) {
-  T W[Sys::D * Sys::D];
-  ros_factor<Sys, Tab, T>(y, p, h, W, piv);
-  put_lds<Sys, T>(W, Wl);
-  ros_stages<Sys, Tab, T, LdsMat<Sys, T>, NSC>(y, p, h, Wl, piv, u, ynew);
+// One step: y_new and, if ERR, the error estimate e.  Where no lane of the
+// wavefront interchanges rows (every trip of the Robertson workloads, 82 % of
+// the HIRES ones at rtol 1e-6 and 59 % at 1e-4, where a column's two largest
+// entries come close) the factorisation and the solves without interchanges
+// and their fill serve, with the same values; otherwise the whole wavefront
+// takes the general ones.  The branch is marked unlikely, so that what the
+// general path has no registers for moves inside it.
+template <class Sys, class Tab, class T, int NSC, bool ERR>
+__device__ __forceinline__ void ros_eval(const T* y, const T* p, T h, T* ynew, T* e) {
+  constexpr int D = Sys::D;
+  PlainMat<Sys, T> F;
+  if (__builtin_expect(!__any(ros_factor_plain<Sys, Tab, T>(y, p, h, F.w)), 1)) {
+    T u[Tab::S][D];
+    int piv[D];
+    ros_stages<Sys, Tab, T, PlainMat<Sys, T>, NSC>(y, p, h, F, piv, u, ynew);
+    if constexpr (ERR) ros_errvec<Tab, D, T>(u, e);
+  } else {
+    T W[D * D], u[Tab::S][D];
+    int piv[D];
+    ros_step<Sys, Tab, T, NSC>(y, p, h, W, piv, u, ynew);
+    if constexpr (ERR) ros_errvec<Tab, D, T>(u, e);
+  }
 }
+
+// The increments u_1..u_SU as the reverse reads them: a register array, or
+// the lane's LDS slots (entry (q, c) at base[(q D + c) * 256 + lane]).  From LDS
+// each stage reads what it needs afresh (fetch is a compiler memory barrier);
+// a read costs half an instruction a double, the moves to and from the
+// accumulation registers, where the array would wait, four.
+template <class T, int D>
+struct RegIncr {
+  const T (*u)[D];
+  __device__ __forceinline__ T operator()(int q, int c) const { return u[q][c]; }
+  __device__ __forceinline__ void fetch() const {}
+};
+template <class T, int D>
+struct LdsIncr {
+  T* base;
+  __device__ __forceinline__ T operator()(int q, int c) const {
+    return base[(q * D + c) * 256 + threadIdx.x];
+  }
+  __device__ __forceinline__ void put(int q, const T* v) const {
+#pragma unroll
+    for (int c = 0; c < D; ++c) base[(q * D + c) * 256 + threadIdx.x] = v[c];
+  }
+  __device__ __forceinline__ void fetch() const { __asm__ __volatile__("" ::: "memory"); }
+};
 
 template <class Tab>
 constexpr bool m_nonzero_below_su() {
@@ -414,8 +427,8 @@ constexpr bool m_nonzero_below_su() {
   return true;
 }
 
-// Reverse of one step (W, piv, u from ros_step at the same y, h; W as a
-// register array or an LdsMat): with the
+// Reverse of one step (W, piv, u from ros_step or ros_factor_plain and
+// ros_stages at the same y, h): with the
 // output cotangent w, lam_in = d(y_new)/dy^T w and gp += d(y_new)/dp^T w.
 //   ubar_i = M_i w + sum_{l>i} (A_li Ybar_l + C_li rbar_l / h)   (l from s down)
 //   rbar_i = W^{-T} ubar_i,  Ybar_i = f_y(Y_i)^T rbar_i,  gp += f_p(Y_i)^T rbar_i
@@ -424,31 +437,54 @@ constexpr bool m_nonzero_below_su() {
 // cotangents are pushed into running sums as they are formed.  Only the SU
 // stages that enter y_new are reversed (a stage that serves the error
 // estimate alone has a zero cotangent).
-template <class Sys, class Tab, class T, class Mat>
+template <class Sys, class Tab, class T, class Mat, class Incr>
 __device__ __forceinline__ void ros_step_vjp(const T* y, const T* p, T h, const Mat& W,
-                                             const int (&piv)[Sys::D],
-                                             const T (&u)[Tab::S][Sys::D], const T* w,
-                                             T* lam_in, T* gp) {
+                                             const int (&piv)[Sys::D], const Incr& u,
+                                             const T* w, T* lam_in, T* gp) {
   constexpr int D = Sys::D, NS = Tab::SU;
   static_assert(m_nonzero_below_su<Tab>(), "every stage sum starts with its M term");
+  // Stages from KEEP up are pulled: their Ybar and rbar / h are kept until
+  // stage KEEP is done, and only then pushed into the sums of the stages
+  // below, which take later ones as they come.  Each sum gets its terms in
+  // the same order either way; with all of them pushed at once, 6 x D sums
+  // and 6 x D increments are live together at the last stage, with this at
+  // most 4 of each (or the kept two stages).
+  constexpr int KEEP = NS >= 4 ? NS - 2 : NS;
   const T hinv = T(1.0) / h;
-  T ub[NS][D], gJ[D];
+  T ub[NS][D], gJ[D], kY[NS][D], kt[NS][D];
 #pragma unroll
   for (int c = 0; c < D; ++c) {
     lam_in[c] = w[c];
     gJ[c] = T(0);
   }
+  auto open = [&](int i) {  // ub_i = M_i w and the kept stages' terms
 #pragma unroll
-  for (int i = 0; i < NS; ++i)
+    for (int c = 0; c < D; ++c) {
+      T acc = T(Tab::M[i]) * w[c];
 #pragma unroll
-    for (int c = 0; c < D; ++c) ub[i][c] = T(Tab::M[i]) * w[c];
+      for (int l = NS - 1; l >= KEEP; --l) {
+        if (l <= i) continue;
+        if (Tab::A[l][i] != 0.0) acc = fmaT(T(Tab::A[l][i]), kY[l][c], acc);
+        if (Tab::C[l][i] != 0.0) acc = fmaT(T(Tab::C[l][i]), kt[l][c], acc);
+      }
+      ub[i][c] = acc;
+    }
+  };
+  if constexpr (KEEP == NS) {
+#pragma unroll
+    for (int i = 0; i < NS; ++i) open(i);
+  }
 #pragma unroll
   for (int i = NS - 1; i >= 0; --i) {
-    T rb[D], tb[D], Yi[D], Yb[D];
+    if (i >= KEEP) open(i);
+    T rb[D], tb[D], Yi[D], Yb[D], ui[D];
+    u.fetch();
 #pragma unroll
-    for (int c = 0; c < D; ++c) rb[c] = ub[i][c];
+    for (int c = 0; c < D; ++c) {
+      rb[c] = ub[i][c];
+      ui[c] = u(i, c);
+    }
     lu_solve_t<Sys, T, Mat>(W, piv, rb);
-    solved_point<Sys, T>(W, rb);
 #pragma unroll
     for (int c = 0; c < D; ++c) tb[c] = hinv * rb[c];
 #pragma unroll
@@ -458,7 +494,7 @@ __device__ __forceinline__ void ros_step_vjp(const T* y, const T* p, T h, const 
 #pragma unroll
       for (int j = 0; j < i; ++j) {
         if (Tab::A[i][j] != 0.0) {
-          acc = first ? T(Tab::A[i][j]) * u[j][c] : fmaT(T(Tab::A[i][j]), u[j][c], acc);
+          acc = first ? T(Tab::A[i][j]) * u(j, c) : fmaT(T(Tab::A[i][j]), u(j, c), acc);
           first = false;
         }
       }
@@ -467,7 +503,19 @@ __device__ __forceinline__ void ros_step_vjp(const T* y, const T* p, T h, const 
     Sys::vjp(Yi, p, rb, Yb, gp);
 #pragma unroll
     for (int c = 0; c < D; ++c) lam_in[c] = lam_in[c] + Yb[c];
-    Sys::jac_vjp(y, p, rb, u[i], gJ, gp);
+    Sys::jac_vjp(y, p, rb, ui, gJ, gp);
+    if (i >= KEEP) {
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        kY[i][c] = Yb[c];
+        kt[i][c] = tb[c];
+      }
+      if (i == KEEP) {
+#pragma unroll
+        for (int j = 0; j < i; ++j) open(j);
+      }
+      continue;
+    }
 #pragma unroll
     for (int j = 0; j < i; ++j) {
 #pragma unroll
@@ -479,6 +527,46 @@ __device__ __forceinline__ void ros_step_vjp(const T* y, const T* p, T h, const 
   }
 #pragma unroll
   for (int c = 0; c < D; ++c) lam_in[c] = lam_in[c] + gJ[c];
+}
+
+// One step from yb recomputed and reversed from its factors: cot(ys, w) gives
+// the cotangent w of the state ys it reaches; lin = d(ys)/dyb^T w,
+// g += d(ys)/dp^T w.  U_LDS (d >= 6): between the two the increments wait in
+// the lane's LDS slots sU.
+template <class Sys, class Tab, class T, bool U_LDS, class Mat, class Cot>
+__device__ __forceinline__ void ros_reverse_of(const T* yb, const T* p, T h, const Mat& W,
+                                               const int (&piv)[Sys::D], T* sU, Cot& cot, T* lin,
+                                               T* g) {
+  constexpr int D = Sys::D;
+  T u[Tab::S][D], ys[D], w[D];
+  ros_stages<Sys, Tab, T, Mat, Tab::SU>(yb, p, h, W, piv, u, ys);
+  if constexpr (U_LDS) {
+    const LdsIncr<T, D> ul{sU};
+#pragma unroll
+    for (int q = 0; q < Tab::SU; ++q) ul.put(q, u[q]);
+    cot(ys, w);
+    ros_step_vjp<Sys, Tab, T>(yb, p, h, W, piv, ul, w, lin, g);
+  } else {
+    cot(ys, w);
+    ros_step_vjp<Sys, Tab, T>(yb, p, h, W, piv, RegIncr<T, D>{u}, w, lin, g);
+  }
+}
+
+// Without interchanges in the wavefront as ros_eval; otherwise the general
+// factorisation.
+template <class Sys, class Tab, class T, bool U_LDS, class Cot>
+__device__ __forceinline__ void ros_reverse(const T* yb, const T* p, T h, T* sU, Cot& cot, T* lin,
+                                            T* g) {
+  constexpr int D = Sys::D;
+  int piv[D];
+  PlainMat<Sys, T> F;
+  if (__builtin_expect(!__any(ros_factor_plain<Sys, Tab, T>(yb, p, h, F.w)), 1)) {
+    ros_reverse_of<Sys, Tab, T, U_LDS>(yb, p, h, F, piv, sU, cot, lin, g);
+  } else {
+    T W[D * D];
+    ros_factor<Sys, Tab, T>(yb, p, h, W, piv);
+    ros_reverse_of<Sys, Tab, T, U_LDS>(yb, p, h, W, piv, sU, cot, lin, g);
+  }
 }
 
 // Mean square (the RMS norm squared) of the scaled error estimate against

@@ -47,9 +47,16 @@ __global__ void serve_setup_kernel(const ServeJob* jobs, int n_jobs, unsigned* n
 }
 
 // PHASE 0 records every tile, PHASE 1 sweeps every tile back: two launches
-// on one stream, so each phase keeps the register budget of its own code.
+// on one stream, so each phase keeps the register budget of its own code (the
+// Rosenbrock methods' as their own kernels ask for it).
 template <class Sys, class Tab, class T, int PHASE>
-__global__ void __launch_bounds__(256) serve_kernel(const ServeJob* jobs, int n_jobs,
+struct ServeBlocks {
+  static constexpr int value = !Tab::ROS    ? 1
+                               : PHASE == 0 ? FwdBlocks<Sys, Tab, T>::value
+                                            : AdjBlocks<Sys, Tab, T, false>::value;
+};
+template <class Sys, class Tab, class T, int PHASE>
+__global__ void __launch_bounds__(256, (ServeBlocks<Sys, Tab, T, PHASE>::value)) serve_kernel(const ServeJob* jobs, int n_jobs,
                                                      int64_t n_tiles, unsigned* next,
                                                      int* flags) {
   __shared__ int64_t s_tile;
