@@ -458,6 +458,36 @@ int launch_forward(const ens_problem* p, int mode, bool ckpt, const FwdArgs& fa,
   return e == hipSuccess ? ENS_OK : hip_fail(e, "save-base launch");
 }
 
+// Whether a record writes each taped step at once (DIRECT) or stages whole
+// lines.  At once up to 65,536 trajectories, one wavefront per SIMD (Lorenz /
+// Tsit5 on [0, 10], ms, staged then direct: 1,000: 0.45, 0.34; 32,768: 0.47,
+// 0.36; 65,536: 0.49, 0.39; 131,072: 0.75, 0.87; Robertson / Rodas4 65,536:
+// 0.34, 0.31), as long as the L2 holds each lane's open line.  Where the
+// trajectories' tapes are a multiple of 16 KiB apart the open lines fall into
+// few of its sets: 32,768 still take 0.35, 65,536 take 0.48 at 16 KiB and
+// 0.54 at 32 KiB, so those are staged from 32,768 on.
+bool direct_record(const FwdArgs& fa) {
+  const int64_t stride = (int64_t)fa.rec.static_pages * fa.rec.page_bytes;
+  return fa.ivp.n <= (stride % 16384 == 0 ? 32768 : 65536);
+}
+
+// A deferred record's save states: one thread per trajectory takes every
+// gridDim.y-th save.  Small ensembles split the saves over the grid's second
+// dimension until there are 1,024 blocks (one wavefront per SIMD): the saves
+// of a trajectory are otherwise a chain of load, step and store.
+dim3 saves_grid(const IvpArgs& v) {
+  const unsigned g = grid_of(v.n), split = (1024 + g - 1) / g;
+  return dim3(g, split < (unsigned)v.n_save ? split : (unsigned)v.n_save);
+}
+
+// Whether any save time lies inside the span, so that a deferred record can
+// leave a save state to be formed.
+bool inner_saves(const IvpArgs& v) {
+  for (int i = 0; i < v.n_save; ++i)
+    if (v.st.t[i] < v.t1) return true;
+  return false;
+}
+
 int launch_forward_body(const ens_problem* p, int mode, bool ckpt, const FwdArgs& fa,
                         hipStream_t st, bool dense) {
   if (p->system == ENS_SYS_LV_UDE) return launch_forward_ude(mode, ckpt, fa, st);
@@ -500,9 +530,9 @@ int launch_forward_body(const ens_problem* p, int mode, bool ckpt, const FwdArgs
       // the explicit pairs' full-tape record forms its save states afterwards
       const int rc = rtc_launch(p->system, p->method, p->dtype,
                                 deferred_expr(p->method, p->dtype), grid_of(fa.ivp.n), fa, st);
-      if (rc != ENS_OK) return rc;
+      if (rc != ENS_OK || !inner_saves(fa.ivp)) return rc;
       return rtc_launch(p->system, p->method, p->dtype, saves_expr(p->method, p->dtype),
-                        grid_of(fa.ivp.n), fa, st);
+                        saves_grid(fa.ivp), fa, st);
     }
     return rtc_launch(p->system, p->method, p->dtype, fwd_expr(p->method, p->dtype, mode, ckpt),
                       grid_of(fa.ivp.n), fa, st);
@@ -515,18 +545,28 @@ int launch_forward_body(const ens_problem* p, int mode, bool ckpt, const FwdArgs
     if constexpr (!Tab::ROS) {
       if (mode == MODE_RECORD && !ckpt) {
         // the explicit pairs' full-tape record forms its save states afterwards
-        hipLaunchKernelGGL((erk_record_deferred_kernel<Sys, Tab, T>), g, b, 0, st, fa);
+        if (direct_record(fa))
+          hipLaunchKernelGGL((erk_record_deferred_kernel<Sys, Tab, T, true>), g, b, 0, st, fa);
+        else
+          hipLaunchKernelGGL((erk_record_deferred_kernel<Sys, Tab, T>), g, b, 0, st, fa);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_fail(e, "record launch");
-        hipLaunchKernelGGL((erk_saves_kernel<Sys, Tab, T>), g, b, 0, st, fa);
+        if (!inner_saves(fa.ivp)) return ENS_OK;
+        hipLaunchKernelGGL((erk_saves_kernel<Sys, Tab, T>), saves_grid(fa.ivp), b, 0, st, fa);
         e = hipGetLastError();
         return e == hipSuccess ? ENS_OK : hip_fail(e, "save-state launch");
       }
     }
     if (mode == MODE_SOLVE)
       hipLaunchKernelGGL((erk_forward_kernel<Sys, Tab, T, MODE_SOLVE, false>), g, b, 0, st, fa);
+    else if (mode == MODE_RECORD && !ckpt && direct_record(fa))
+      hipLaunchKernelGGL((erk_forward_kernel<Sys, Tab, T, MODE_RECORD, false, false, true>), g, b,
+                         0, st, fa);
     else if (mode == MODE_RECORD && !ckpt)
       hipLaunchKernelGGL((erk_forward_kernel<Sys, Tab, T, MODE_RECORD, false>), g, b, 0, st, fa);
+    else if (mode == MODE_RECORD && direct_record(fa))
+      hipLaunchKernelGGL((erk_forward_kernel<Sys, Tab, T, MODE_RECORD, true, false, true>), g, b,
+                         0, st, fa);
     else if (mode == MODE_RECORD)
       hipLaunchKernelGGL((erk_forward_kernel<Sys, Tab, T, MODE_RECORD, true>), g, b, 0, st, fa);
     else if (mode == MODE_REFRESH && !ckpt)

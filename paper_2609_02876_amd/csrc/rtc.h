@@ -238,14 +238,14 @@ int rtc_function(int sys, int method, int dtype, const std::string& expr, hipFun
 // Launch one kernel of a registered system: BLOCK lanes per block, the
 // argument struct passed by value.
 template <class Args>
-int rtc_launch(int sys, int method, int dtype, const std::string& expr, unsigned grid,
+int rtc_launch(int sys, int method, int dtype, const std::string& expr, dim3 grid,
                const Args& args, hipStream_t st) {
   hipFunction_t f;
   const int rc = rtc_function(sys, method, dtype, expr, &f);
   if (rc != ENS_OK) return rc;
   void* params[] = {const_cast<Args*>(&args)};
   const hipError_t e =
-      hipModuleLaunchKernel(f, grid, 1, 1, BLOCK, 1, 1, 0, st, params, nullptr);
+      hipModuleLaunchKernel(f, grid.x, grid.y, 1, BLOCK, 1, 1, 0, st, params, nullptr);
   return e == hipSuccess ? ENS_OK : hip_fail(e, "launch of a registered system's kernel");
 }
 
