@@ -276,6 +276,19 @@ __device__ __forceinline__ double mean_sq(const double* v, const double* sc) {
   return ss * (1.0 / (double)D);
 }
 
+// max(|a|, |b|) in one instruction, of operands that are no signalling NaN
+// (fmax would canonicalise both first).  A NaN operand gives the other one.
+__device__ __forceinline__ double max_abs(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float max_abs(float a, float b) {
+  float r;
+  asm("v_max_f32_e64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
 // Mean square of the error estimate e = h * esum against atol + rtol
 // max(|y|, |y_new|).
 template <class T, int D>
@@ -285,7 +298,7 @@ __device__ __forceinline__ double err_ms_sum(const T* y, const T* ynew, double h
 #pragma unroll
   for (int c = 0; c < D; ++c) {
     e[c] = h * esum[c];
-    sc[c] = fmaT(rtol, fmax(fabs((double)y[c]), fabs((double)ynew[c])), atol);
+    sc[c] = fmaT(rtol, (double)max_abs(y[c], ynew[c]), atol);
   }
   return mean_sq<D>(e, sc);
 }
@@ -306,8 +319,8 @@ __device__ __forceinline__ double ipow(double y) {
 // The proposed step factor 0.9 ms^(-1/K2), K2 = 2 (q + 1) for an embedded
 // order q.  ms is held to [1e-30, 1e30] first: the factor is clamped to
 // [0.2, 10] long before either end (with K2 >= 6 the ends give factors
-// beyond 90 and below 0.01).  A NaN ms gives 0, so that a trial whose
-// error is not a number shrinks h by the lower bound.  The seed
+// beyond 90 and below 0.01).  The caller replaces the factor of a NaN ms by
+// the lower bound.  The seed
 // 2^(-log2(x) / K2) in single precision is within a few 1e-7; one Newton
 // step y <- y + (y / K2)(1 - x y^K2) takes it to about 1e-13.
 template <int K2>
@@ -318,7 +331,7 @@ __device__ __forceinline__ double step_factor(double ms) {
   constexpr double inv_k = 1.0 / (double)K2;
   const double t = fmaT(-x, ipow<K2>(y), 1.0);
   const double yr = fmaT(y * inv_k, t, y);
-  return ms >= 0.0 ? 0.9 * yr : 0.0;
+  return 0.9 * yr;
 }
 
 // x^(-1/K) for the controller and the starting step (K = 3..8), from
@@ -773,24 +786,44 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   }
 
   // Side steps of the save times.  After a step is accepted whose interval
-  // holds save times, the new state is held back (yn, kn at tn) and the
+  // holds save times, the new state is held back in LDS (at tn) and the
   // following iterations take the side steps from the unchanged base (y, k1
   // at t); the last one commits the new state.  So every evaluation starts
   // from (y, k1), with no per-iteration select between two bases.
-  T yn[D], kn[D];
-  double tn = t0;
+  // In LDS because the lanes that hold no state back are most of them: in
+  // registers the held values were moved about in every iteration.  (Wider
+  // registered systems keep them in registers: their staged records fill the
+  // LDS.)
+  constexpr int HELD = DEFER || DENSE ? 0 : (Tab::FSAL ? 2 : 1) * D;
+  constexpr bool HELD_LDS = HELD > 0 && D <= 8;
+  __shared__ T s_held[HELD_LDS ? HELD * 256 : 1];
+  __shared__ double s_tn[HELD_LDS ? 256 : 1];
+  T r_held[HELD_LDS || HELD == 0 ? 1 : HELD];
+  double r_tn = t0;
+  auto held_at = [&](int q) -> T& {
+    if constexpr (HELD_LDS)
+      return s_held[q * 256 + threadIdx.x];
+    else
+      return r_held[q];
+  };
+  auto held_tn = [&]() -> double& {
+    if constexpr (HELD_LDS)
+      return s_tn[threadIdx.x];
+    else
+      return r_tn;
+  };
   if constexpr (MODE != MODE_SOLVE) R.first_page[tr] = -1;
   int next_save = 0;
-  // running pointers to this lane's next save-state slots
-  T* ys_out = ysv + tr;
-  // the base state of the save at ys_out, into the record's save_base.  The
-  // given-mesh modes on a full tape leave it to a kernel that copies the
+  // This lane's slots of the next save are found from next_save at each use:
+  // saves are few, and running pointers were moved about in every iteration.
+  // put_base: the base state of the next save, into the record's save_base.
+  // The given-mesh modes on a full tape leave it to a kernel that copies the
   // states from the tape afterwards: their loops load a step size per step,
   // and those loads would wait behind these stores.
   auto put_base = [&](const T* yb, bool valid) {
     if constexpr (MODE == MODE_RECORD || (CKPT && MODE != MODE_SOLVE) ||
                   (DENSE && MODE != MODE_SOLVE)) {
-      T* sb = (T*)R.save_base + (ys_out - ysv);
+      T* sb = (T*)R.save_base + ((int64_t)next_save * D * n + tr);
 #pragma unroll
       for (int c = 0; c < D; ++c) sb[c * n] = valid ? yb[c] : T(NAN);
     }
@@ -798,78 +831,87 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   // dense output: the step's end state and its size, beside the base state
   auto put_dense = [&](const T* y1, double hstep) {
     if constexpr (DENSE && MODE != MODE_SOLVE) {
-      T* sb = (T*)R.save_base_hi + (ys_out - ysv);
+      T* sb = (T*)R.save_base_hi + ((int64_t)next_save * D * n + tr);
 #pragma unroll
       for (int c = 0; c < D; ++c) sb[c * n] = y1[c];
       R.save_h[(int64_t)next_save * n + tr] = hstep;
     }
   };
-  int32_t* sidx_out = R.save_idx + tr;
-  double* sdt_out = R.save_dt + tr;
-  const int64_t ys_stride = (int64_t)D * n;
+  // the next save's mesh index and offset
+  auto put_point = [&](int32_t index, double offset) {
+    if constexpr (MODE != MODE_SOLVE) {
+      const int64_t q = (int64_t)next_save * n + tr;
+      R.save_idx[q] = index;
+      R.save_dt[q] = offset;
+    }
+  };
+  auto put_state = [&](const T* yv, bool valid) {
+    T* ys = ysv + ((int64_t)next_save * D * n + tr);
+#pragma unroll
+    for (int c = 0; c < D; ++c) ys[c * n] = valid ? yv[c] : T(NAN);
+  };
   double ts = s_times[0];
   bool side = false;
   int32_t S = 0, trials = 0;
   bool prev_rej = false;
-  int32_t page = -1;
-  char* pg = nullptr;
-  int slot = 0, kpage = 0;  // position of the next taped step: S = K kpage + slot
+  // The tape.  A trajectory's reserved pages follow one another, so in them
+  // the next place is found by adding: `tape` is where the next step goes
+  // (CKPT: the current page), and only when the `room` steps (CKPT: pages)
+  // there are used up does a lane take an overflow page.  K is a power of two.
+  int32_t page = -1;  // the last overflow page taken
+  uint32_t room = 0;
+  char* tape = nullptr;
+  if constexpr (MODE != MODE_SOLVE) {
+    tape = R.pages + tr * R.static_pages * R.page_bytes - (CKPT ? R.page_bytes : 0);
+    // (a step count is below 2^31)
+    const int64_t r = CKPT ? (int64_t)R.static_pages : (int64_t)R.static_pages * PAGE_STEPS;
+    room = r < 0xffffffff ? (uint32_t)r : 0xffffffffu;
+  }
   // the trial budget as a 32-bit count (trials never exceed it)
   const int32_t max_trials =
       a.ivp.max_steps < 0x7fffffff ? (int32_t)a.ivp.max_steps : 0x7fffffff;
 
-  // one iteration of a lane's loop (a `return` ends the iteration)
+  const double h_floor = 16.0 * EPS64 * fmax(fmax(fabs(t0), fabs(t1)), 1.0);
+
+  // The loop is bound by vector instructions at large n and by the length of
+  // a trial's chain at small n, so it is kept to the arithmetic: beside that
+  // a trial of the Lorenz / Tsit5 solve issued 56 register moves, now 17
+  // (2^20 trajectories on [0, 1]: 0.405 -> 0.362 ms; a record of 1,000 on
+  // [0, 10]: 0.33 -> 0.28).
+  // live: whether a lane goes on, checked before each step but not before a
+  // side step; out of the iteration so that this holds no early return.
   auto live = [&]() {
-    return status == LANE_OK && (side || (MODE == MODE_FROZEN ? (S < S_mesh) : (t < t1)));
-  };
-  auto iteration = [&]() {
-    double hh;
-    bool last = false;
-    if (!side) {
-      if constexpr (MODE == MODE_FROZEN) {
-        hh = h_next;
-        last = (S == S_mesh - 1);
-        if (!last) h_next = a.mesh_h[(int64_t)(S + 1) * n + tr];
-        ++trials;
-      } else if constexpr (MODE == MODE_REFRESH) {
-        if (trials >= max_trials) {
-          status = LANE_MAX_STEPS;
-          return;  // the lane's loop ends here
-        }
-        if (following) {  // the old mesh's step, its last one ending at t1
-          h = h_next;
-          last = (S == S_mesh - 1);
-          if (!last) h_next = a.mesh_h[(int64_t)(S + 1) * n + tr];
-        } else {
-          if (h < 16.0 * EPS64 * fmax(fabs(t), 1.0)) {
-            status = LANE_DT_UNDERFLOW;
-            return;  // the lane's loop ends here
-          }
-          if (t + h >= t1) {
-            h = t1 - t;
-            last = true;
-          }
-        }
-        ++trials;
-        hh = h;
-      } else {
-        if (trials >= max_trials) {
-          status = LANE_MAX_STEPS;
-          return;  // the lane's loop ends here
-        }
-        if (h < 16.0 * EPS64 * fmax(fabs(t), 1.0)) {
-          status = LANE_DT_UNDERFLOW;
-          return;  // the lane's loop ends here
-        }
-        ++trials;
-        if (t + h >= t1) {
-          h = t1 - t;
-          last = true;
-        }
-        hh = h;
+    if constexpr (MODE == MODE_FROZEN) return status == LANE_OK && (side || S < S_mesh);
+    bool go = status == LANE_OK && (side || t < t1);
+    if (go && !side && (trials >= max_trials || h < h_floor)) {
+      if (trials >= max_trials) {
+        status = LANE_MAX_STEPS;
+      } else if (!following && h < 16.0 * EPS64 * fmax(fabs(t), 1.0)) {
+        status = LANE_DT_UNDERFLOW;
       }
-    } else {
+      go = status == LANE_OK;
+    }
+    return go;
+  };
+  // one iteration of a lane's loop
+  auto iteration = [&]() {
+    double hh, tnew;
+    if (side) {
       hh = ts - t;
+      tnew = t1;
+    } else {
+      if constexpr (MODE != MODE_FROZEN) {
+        tnew = t + h;
+        hh = tnew >= t1 ? t1 - t : h;
+        tnew = fmin(tnew, t1);
+      }
+      if (MODE == MODE_FROZEN || following) {  // the mesh's step, its last one ending at t1
+        hh = h_next;
+        const bool last = (S == S_mesh - 1);
+        tnew = last ? t1 : t + hh;
+        if (!last) h_next = a.mesh_h[(int64_t)(S + 1) * n + tr];
+      }
+      ++trials;
     }
 
     // one evaluation of the step map from the base (y, k1); err is the mean
@@ -907,125 +949,112 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
       if constexpr (MODE != MODE_FROZEN) err = err_ms_sum<T, D>(y, ynew, hh, esum, rtol, atol);
     }
 
+    bool commit = false;  // (ynew, klast) at tnew becomes the state
+    bool acc = false;
     if (side) {
-#pragma unroll
-      for (int c = 0; c < D; ++c) ys_out[c * n] = ynew[c];
+      put_state(ynew, true);
       put_base(y, true);
-      ys_out += ys_stride;
-      if constexpr (MODE != MODE_SOLVE) {
-        *sidx_out = S - 1;
-        *sdt_out = hh;
-        sidx_out += n;
-        sdt_out += n;
-      }
+      put_point(S - 1, hh);
       ++next_save;
       ts = s_times[next_save];
-      side = ts < tn;
-      if (!side) {  // the last save of the interval: commit the new state
+      tnew = held_tn();
+      side = ts < tnew;
+      if (!side) {  // the last save of the interval: the new state held back
+        commit = true;
 #pragma unroll
         for (int c = 0; c < D; ++c) {
-          y[c] = yn[c];
-          if constexpr (Tab::FSAL) k1[c] = kn[c];
+          ynew[c] = held_at(c);
+          if constexpr (Tab::FSAL) klast[c] = held_at(D + c);
         }
-        t = tn;
       }
-      return;
-    }
-
-    // proposed factor 0.9 err^(-1/(q+1)), formed once for both outcomes
-    double fac0 = 0.0;
-    if constexpr (MODE != MODE_FROZEN) fac0 = step_factor<2 * (Tab::QEMB + 1)>(err);
-    if constexpr (MODE == MODE_REFRESH) {
-      if (following && !(err <= slack2)) {  // the old mesh ends here: a rejected trial
-        following = false;
-        kept = S;
-        h = hh * fmax(0.2, fac0);
-        prev_rej = true;
-        return;
-      }
-    }
-    if (MODE == MODE_FROZEN || (MODE == MODE_REFRESH && following) || err <= 1.0) {
-      if constexpr (MODE != MODE_SOLVE) {
-        const bool need = (slot == 0);
-        const bool over = need && (kpage >= R.static_pages);
-        const uint64_t got = wave_bump(&R.counters[CNT_PAGES], over);
-        if (need) {
-          int32_t np_;
-          if (!over) {
-            np_ = (int32_t)(tr * R.static_pages + kpage);
-          } else {
-            if (got >= (uint64_t)(R.n_pages - R.n_static)) {
-              status = LANE_NOSPACE;
-              return;  // the lane's loop ends here
-            }
-            np_ = (int32_t)(R.n_static + (int64_t)got);
-            const int64_t li = (int64_t)np_ - R.n_static;
-            R.links[2 * li] = page;
-            R.links[2 * li + 1] = -1;
-            if (page >= R.n_static)
-              R.links[2 * ((int64_t)page - R.n_static) + 1] = np_;
-            else
-              R.first_page[tr] = np_;
+    } else {
+      acc = MODE == MODE_FROZEN || err <= 1.0;
+      if constexpr (MODE == MODE_REFRESH) {
+        if (following) {
+          acc = err <= slack2;
+          if (!acc) {  // the old mesh ends here: a rejected trial
+            following = false;
+            kept = S;
           }
-          page = np_;
-          pg = R.pages + (int64_t)page * R.page_bytes;
         }
+      }
+      // the proposed factor 0.9 err^(-1/(q+1)), held to [0.2, 10] after an
+      // accepted trial, [0.2, 1] if the one before was rejected, and to at
+      // least 0.2 after a rejected one, whose error may be NaN (then 0.2)
+      if constexpr (MODE != MODE_FROZEN) {
+        const double cap = acc ? (prev_rej ? 1.0 : 10.0) : (err >= 0.0 ? INFINITY : 0.0);
+        h = hh * fmax(0.2, fmin(cap, step_factor<2 * (Tab::QEMB + 1)>(err)));
+        prev_rej = !acc;
+      }
+    }
+    if constexpr (MODE != MODE_SOLVE) {
+      if (acc && room == 0 && (S & (K - 1)) == 0) {
+        const uint64_t got = wave_bump(&R.counters[CNT_PAGES], true);
+        if (got >= (uint64_t)(R.n_pages - R.n_static)) {
+          status = LANE_NOSPACE;  // the lane's loop ends here
+          acc = false;
+        } else {
+          const int32_t np_ = (int32_t)(R.n_static + (int64_t)got);
+          R.links[2 * got] =
+              page >= 0 ? page : S > 0 ? (int32_t)((tr + 1) * R.static_pages - 1) : -1;
+          R.links[2 * got + 1] = -1;
+          if (page >= 0)
+            R.links[2 * ((int64_t)page - R.n_static) + 1] = np_;
+          else
+            R.first_page[tr] = np_;
+          page = np_;
+          tape = R.pages + (int64_t)page * R.page_bytes - (CKPT ? R.page_bytes : 0);
+          room = CKPT ? 1 : PAGE_STEPS;
+        }
+      }
+    }
+    if (acc) {
+      if constexpr (MODE != MODE_SOLVE) {
         if constexpr (CKPT) {
-          if (need) store_state<T, D>(pg, y);
+          const int slot = S & (K - 1);
+          if (slot == 0) {
+            tape += R.page_bytes;
+            --room;
+            store_state<T, D>(tape, y);
+          }
           if constexpr (DIRECT) {
-            reinterpret_cast<double*>(pg + YB)[slot] = hh;
+            reinterpret_cast<double*>(tape + YB)[slot] = hh;
           } else {
             s_h[(slot & (H_GROUP - 1)) * 256 + threadIdx.x] = hh;
             if ((slot & (H_GROUP - 1)) == H_GROUP - 1)
-              flush_h(s_h, H_GROUP, pg + YB + (slot - (H_GROUP - 1)) * 8);
+              flush_h(s_h, H_GROUP, tape + YB + (slot - (H_GROUP - 1)) * 8);
           }
         } else {
+          const int q = S & (TAPE_GROUP - 1);  // the step's place in its group
+          char* gp = tape - (TAPE_GROUP - 1) * RB;  // the group, at its last step
           if constexpr (DIRECT) {
-            store_rec<T, D>(pg + slot * RB, hh, y);
+            store_rec<T, D>(tape, hh, y);
           } else if constexpr (COOP) {
-            stage_rec_sw<T, D>(s_tape, (slot & (TAPE_GROUP - 1)) * CH, hh, y);
-            if ((slot & (TAPE_GROUP - 1)) == TAPE_GROUP - 1)
-              flush_gp = pg + (slot - (TAPE_GROUP - 1)) * RB;
-          } else if ((slot & (TAPE_GROUP - 1)) == TAPE_GROUP - 1) {
-            char* gp = pg + (slot - (TAPE_GROUP - 1)) * RB;
+            stage_rec_sw<T, D>(s_tape, q * CH, hh, y);
+            if (q == TAPE_GROUP - 1) flush_gp = gp;
+          } else if (q == TAPE_GROUP - 1) {
             flush_recs<T, D>(s_tape, TAPE_GROUP - 1, gp);
-            store_rec<T, D>(gp + (TAPE_GROUP - 1) * RB, hh, y);
+            store_rec<T, D>(tape, hh, y);
           } else {
-            stage_rec<T, D>(s_tape, (slot & (TAPE_GROUP - 1)) * CH, hh, y);
+            stage_rec<T, D>(s_tape, q * CH, hh, y);
           }
-        }
-        if (++slot == K) {
-          slot = 0;
-          ++kpage;
+          tape += RB;
+          --room;
         }
       }
       ++S;
-      const double tnew = last ? t1 : t + hh;
-      if constexpr (MODE != MODE_FROZEN) {
-        h = hh * fmax(0.2, fmin(prev_rej ? 1.0 : 10.0, fac0));
-        prev_rej = false;
-      }
+      commit = true;
       if constexpr (DENSE && MODE != MODE_SOLVE) {
         // saves inside this step: the step's end states, size and the save's
         // offset are noted, and dense_saves_kernel forms the states from
         // them afterwards, all (trajectory, save) pairs in parallel
         while (ts < tnew) {
-          *sidx_out = S - 1;
-          *sdt_out = ts - t;
-          sidx_out += n;
-          sdt_out += n;
+          put_point(S - 1, ts - t);
           put_base(y, true);
           put_dense(ynew, hh);
-          ys_out += ys_stride;
           ++next_save;
           ts = s_times[next_save];
         }
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-          y[c] = ynew[c];
-          if constexpr (Tab::FSAL) k1[c] = klast[c];
-        }
-        t = tnew;
       } else if constexpr (DENSE) {
         // the solve keeps nothing: saves inside this step take the step's
         // continuous extension at once
@@ -1043,117 +1072,89 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
           }
           while (ts < tnew) {
             hermite_state<T, D>(y, ynew, f0, f1, hh, ts - t, yd);
-#pragma unroll
-            for (int c = 0; c < D; ++c) ys_out[c * n] = yd[c];
-            if constexpr (MODE != MODE_SOLVE) {
-              *sidx_out = S - 1;
-              *sdt_out = ts - t;
-              sidx_out += n;
-              sdt_out += n;
-            }
-            put_base(y, true);
-            put_dense(ynew, hh);
-            ys_out += ys_stride;
+            put_state(yd, true);
             ++next_save;
             ts = s_times[next_save];
           }
         }
-#pragma unroll
-        for (int c = 0; c < D; ++c) {
-          y[c] = ynew[c];
-          if constexpr (Tab::FSAL) k1[c] = klast[c];
-        }
-        t = tnew;
       } else if constexpr (DEFER) {
         // saves inside this step: base index S - 1 and offset from its start
         while (ts < tnew) {
-          *sidx_out = S - 1;
-          *sdt_out = ts - t;
-          sidx_out += n;
-          sdt_out += n;
+          put_point(S - 1, ts - t);
           put_base(y, true);
-          ys_out += ys_stride;
           ++next_save;
           ts = s_times[next_save];
         }
+      } else if (ts < tnew) {
+        side = true;
+        commit = false;
 #pragma unroll
         for (int c = 0; c < D; ++c) {
-          y[c] = ynew[c];
-          if constexpr (Tab::FSAL) k1[c] = klast[c];
+          held_at(c) = ynew[c];
+          if constexpr (Tab::FSAL) held_at(D + c) = klast[c];
         }
-        t = tnew;
-      } else {
-        side = ts < tnew;
-        if (side) {
-#pragma unroll
-          for (int c = 0; c < D; ++c) {
-            yn[c] = ynew[c];
-            if constexpr (Tab::FSAL) kn[c] = klast[c];
-          }
-          tn = tnew;
-        } else {
-#pragma unroll
-          for (int c = 0; c < D; ++c) {
-            y[c] = ynew[c];
-            if constexpr (Tab::FSAL) k1[c] = klast[c];
-          }
-          t = tnew;
-        }
+        held_tn() = tnew;
       }
-    } else {
-      h = hh * fmax(0.2, fac0);
-      prev_rej = true;
+    }
+    // one block for every way here, held together: split up by the ways, it
+    // copied the state on those that do not commit
+    int held = commit;
+    asm volatile("" : "+v"(held));
+    if (held != 0) {
+#pragma unroll
+      for (int c = 0; c < D; ++c) {
+        y[c] = ynew[c];
+        if constexpr (Tab::FSAL) k1[c] = klast[c];
+      }
+      t = tnew;
     }
   };
   if constexpr (COOP) {
     // the loop runs while any lane of the wavefront is live: lanes that are
     // done stay to help write the groups
     const WaveFlush wf = wave_flush_parts<T, D>();
-    for (;;) {
-      const bool act = live();
-      if (!__any(act)) break;
-      if (act) iteration();
-      flush_groups_wave<T, D>(s_tape, s_wq, wf, flush_gp);
+    bool act = live();
+    if (__any(act)) {
+      do {
+        if (act) iteration();
+        flush_groups_wave<T, D>(s_tape, s_wq, wf, flush_gp);
+        act = live();
+      } while (__any(act));
     }
-  } else {
-    while (live()) iteration();
+  } else if (live()) {
+    // (tested at the end: a test at the head copied the state in every trip)
+    do {
+      iteration();
+    } while (live());
   }
 
-  // records of an unfinished group (S = K kpage + slot; groups never
-  // straddle a page because K is a multiple of the group size)
+  // records of an unfinished group (groups never straddle a page because K
+  // is a multiple of the group size)
   if constexpr (MODE != MODE_SOLVE && !DIRECT) {
-    if constexpr (CKPT) {
-      const int rem = S % H_GROUP;
-      if (rem > 0 && pg != nullptr) flush_h(s_h, rem, pg + YB + (slot - rem) * 8);
-    } else {
-      const int rem = S % TAPE_GROUP;
-      if constexpr (COOP) {
-        if (rem > 0 && pg != nullptr) flush_recs_sw<T, D>(s_tape, rem, pg + (slot - rem) * RB);
-      } else {
-        if (rem > 0 && pg != nullptr) flush_recs<T, D>(s_tape, rem, pg + (slot - rem) * RB);
-      }
+    const int rem = S & ((CKPT ? H_GROUP : TAPE_GROUP) - 1);
+    if (rem > 0) {
+      if constexpr (CKPT)
+        flush_h(s_h, rem, tape + YB + ((S & (K - 1)) - rem) * 8);
+      else if constexpr (COOP)
+        flush_recs_sw<T, D>(s_tape, rem, tape - rem * RB);
+      else
+        flush_recs<T, D>(s_tape, rem, tape - rem * RB);
     }
   }
 
   // saves at the last mesh point (t_s = t1): a side step of size zero
   const bool ok = (status == LANE_OK);
   for (; next_save < ns; ++next_save) {
-#pragma unroll
-    for (int c = 0; c < D; ++c) ys_out[c * n] = ok ? y[c] : T(NAN);
+    put_state(y, ok);
     put_base(y, ok);
     put_dense(y, 0.0);
-    ys_out += ys_stride;
-    if constexpr (MODE != MODE_SOLVE) {
-      *sidx_out = ok ? S : -1;
-      *sdt_out = ok ? s_times[next_save] - t : NAN;
-      sidx_out += n;
-      sdt_out += n;
-    }
+    put_point(ok ? S : -1, ok ? s_times[next_save] - t : NAN);
   }
   if constexpr (MODE != MODE_SOLVE) {
     R.steps[tr] = S;
     R.n_trial[tr] = trials;
-    R.last_page[tr] = page;
+    R.last_page[tr] =
+        page >= 0 ? page : S > 0 ? (int32_t)(tr * R.static_pages + (S - 1) / K) : -1;
     R.status[tr] = status;
 #pragma unroll
     for (int c = 0; c < D; ++c) ((T*)R.y_final)[c * n + tr] = y[c];

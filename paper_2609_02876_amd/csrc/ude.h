@@ -506,7 +506,7 @@ __global__ void __launch_bounds__(256, 2) ude_forward_kernel(const FwdArgs a) {
     double err = 0.0, fac0 = 0.0;
     if constexpr (MODE != MODE_FROZEN) {
       err = err_ms_sum<T, D>(yb, ynew, hh, esum, rtol, atol);  // RMS norm squared
-      fac0 = step_factor<2 * (Tab::QEMB + 1)>(err);
+      fac0 = err >= 0.0 ? step_factor<2 * (Tab::QEMB + 1)>(err) : 0.0;
     }
     if (!act) continue;
 
