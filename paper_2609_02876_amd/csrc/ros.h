@@ -40,14 +40,32 @@ constexpr unsigned jac_row_of(int, long) {
   return (1u << S::D) - 1u;
 }
 
+// The one interchange that the factorisation without the general ones still
+// makes: in column SWAP[0], of that row and row SWAP[1], where the system
+// declares it, else none.  (HIRES: column 1 holds 8.75 + 1 / (gamma h) less a
+// little in row 1 and 8.32 in row 3, so rows 1 and 3 change places once h is
+// large; of 430 interchanges in 128 trajectories at rtol 1e-6 354 are this one,
+// and it makes one more entry of U and one of L possible.)
+struct SwapAt {
+  int col, row;
+};
+template <class S>
+constexpr auto swap_of(int) -> decltype(S::SWAP[0], SwapAt{}) {
+  return SwapAt{S::SWAP[0], S::SWAP[1]};
+}
+template <class S>
+constexpr SwapAt swap_of(long) {
+  return SwapAt{-1, -1};
+}
+
 // What partial pivoting can make of W's pattern, step by step.  Rows are
 // bitmasks of the columns that may be nonzero.  Step k: the rows at or
 // below k with a possibly nonzero column-k entry are the pivot candidates;
 // the interchange may give row k any candidate's pattern and a candidate
 // row k's; then each row below k with a possibly nonzero column-k entry is
 // eliminated, taking on the pivot row's pattern right of column k.  PIV
-// false: the pattern where nothing is interchanged (row k is the only
-// candidate of column k).
+// false: the pattern where nothing but the system's SWAP is interchanged (row
+// k is the only other candidate of column k).
 template <int D>
 struct LuPattern {
   unsigned cand[D];    // step k: candidate pivot rows (bit i), row k included
@@ -67,7 +85,8 @@ constexpr LuPattern<Sys::D> lu_pattern() {
     for (int i = 0; i < D; ++i) P.before[k][i] = M[i];
     unsigned cand = 1u << k, any = M[k];
     for (int i = k + 1; i < D; ++i)
-      if (PIV && ((M[i] >> k) & 1u)) {
+      if ((PIV || (k == swap_of<Sys>(0).col && i == swap_of<Sys>(0).row)) &&
+          ((M[i] >> k) & 1u)) {
         cand |= 1u << i;
         any |= M[i];
       }
@@ -147,32 +166,68 @@ __device__ __forceinline__ void ros_factor(const T* y, const T* p, T h, T (&W)[S
   }
 }
 
-// The factorisation where every column's pivot is on the diagonal: the same
-// operations as ros_factor's on a lane that interchanges nothing (what that
-// does on the fill of other pivot orders adds exact zeros).  Returns whether
-// the lane would have interchanged rows, in which case the factors are not
-// ros_factor's.
+// The factors without the general interchanges, indexed as the register array
+// they are in; the solves take them with the smaller pattern.
+template <class Sys, class T>
+struct PlainMat {
+  T w[Sys::D * Sys::D];
+  bool sw;  // whether the system's SWAP was made
+  __device__ __forceinline__ T operator[](int e) const { return w[e]; }
+};
+
+// Rows a and b of a vector interchanged where sw.
+template <class T>
+__device__ __forceinline__ void swap_where(bool sw, T& a, T& b) {
+  const T t = a;
+  a = pick(sw, b, a);
+  b = pick(sw, t, b);
+}
+
+// The factorisation where every column's pivot is on the diagonal, or is the
+// system's SWAP: the same operations as ros_factor's on a lane that makes no
+// other interchange (what that does on the fill of other pivot orders adds
+// exact zeros).  Returns whether the lane would have made one, in which case
+// the factors are not ros_factor's.
 template <class Sys, class Tab, class T>
 __device__ __forceinline__ bool ros_factor_plain(const T* y, const T* p, T h,
-                                                 T (&W)[Sys::D * Sys::D]) {
+                                                 PlainMat<Sys, T>& F) {
   constexpr int D = Sys::D;
   constexpr LuPattern<D> P = lu_pattern<Sys, false>();
+  constexpr SwapAt SW = swap_of<Sys>(0);
+  T(&W)[D * D] = F.w;
   Sys::jac(y, p, W);
   const T dg = T(1.0) / (T(Tab::GAMMA) * h);
 #pragma unroll
   for (int i = 0; i < D * D; ++i) W[i] = -W[i];
 #pragma unroll
   for (int i = 0; i < D; ++i) W[i * D + i] = W[i * D + i] + dg;
-  bool sw = false;
+  bool other = false;
+  F.sw = false;
 #pragma unroll
   for (int k = 0; k < D; ++k) {
-    const T best = fabs(W[k * D + k]);
+    T best = fabs(W[k * D + k]);
+    if (k == SW.col) {
+      const T v = fabs(W[SW.row * D + k]);
+      F.sw = v > best;
+      best = pick(F.sw, v, best);
+      // the first of the largest is the pivot
+#pragma unroll
+      for (int i = k + 1; i < D; ++i)
+        if (has(P.elim[k], i) && i != SW.row) {
+          const T o = fabs(W[i * D + k]);
+          other |= o > best || (i < SW.row && F.sw && o == best);
+        }
+#pragma unroll
+      for (int j = 0; j < D; ++j)
+        if (has(P.before[k][k] | P.before[k][SW.row], j))
+          swap_where(F.sw, W[k * D + j], W[SW.row * D + j]);
+    }
     const T r = T(1.0) / W[k * D + k];
     W[k * D + k] = r;
 #pragma unroll
     for (int i = k + 1; i < D; ++i) {
       if (!has(P.elim[k], i)) continue;  // its multiplier is zero
-      sw |= fabs(W[i * D + k]) > best;
+      if (k != SW.col) other |= fabs(W[i * D + k]) > best;
       const T l = W[i * D + k] * r;
       W[i * D + k] = l;
 #pragma unroll
@@ -180,16 +235,9 @@ __device__ __forceinline__ bool ros_factor_plain(const T* y, const T* p, T h,
         if (has(P.pivrow[k], j)) W[i * D + j] = fmaT(-l, W[k * D + j], W[i * D + j]);
     }
   }
-  return sw;
+  return other;
 }
 
-// The factors of ros_factor_plain: indexed as the register array they are in;
-// the solves take them without interchanges and with the smaller pattern.
-template <class Sys, class T>
-struct PlainMat {
-  T w[Sys::D * Sys::D];
-  __device__ __forceinline__ T operator[](int e) const { return w[e]; }
-};
 template <class Mat>
 struct Pivoted {
   static constexpr bool value = true;
@@ -242,7 +290,11 @@ template <class Sys, class T, class Mat>
 __device__ __forceinline__ void lu_solve(const Mat& W, const int (&piv)[Sys::D], T* x) {
   constexpr int D = Sys::D;
   constexpr LuPattern<D> P = lu_pattern<Sys, Pivoted<Mat>::value>();
-  if constexpr (Pivoted<Mat>::value) permute_fwd<Sys, T>(piv, x);
+  constexpr SwapAt SW = swap_of<Sys>(0);
+  if constexpr (Pivoted<Mat>::value)
+    permute_fwd<Sys, T>(piv, x);
+  else if constexpr (SW.col >= 0)
+    swap_where(W.sw, x[SW.col], x[SW.row]);
 #pragma unroll
   for (int i = 0; i < D; ++i) {
     T acc = x[i];
@@ -283,7 +335,11 @@ __device__ __forceinline__ void lu_solve_t(const Mat& W, const int (&piv)[Sys::D
       if (has(P.fin[j], i)) acc = fmaT(-W[j * D + i], z[j], acc);
     z[i] = acc;
   }
-  if constexpr (Pivoted<Mat>::value) permute_bwd<Sys, T>(piv, z);
+  constexpr SwapAt SW = swap_of<Sys>(0);
+  if constexpr (Pivoted<Mat>::value)
+    permute_bwd<Sys, T>(piv, z);
+  else if constexpr (SW.col >= 0)
+    swap_where(W.sw, z[SW.col], z[SW.row]);
 }
 
 // Stage input Y_i = y + sum_{j<i} A_ij u_j (index order, first term a
@@ -373,17 +429,19 @@ __device__ __forceinline__ void ros_errvec(const T (&u)[Tab::S][D], T* e) {
 }
 
 // One step: y_new and, if ERR, the error estimate e.  Where no lane of the
-// wavefront interchanges rows (every trip of the Robertson workloads, 82 % of
-// the HIRES ones at rtol 1e-6 and 59 % at 1e-4, where a column's two largest
-// entries come close) the factorisation and the solves without interchanges
-// and their fill serve, with the same values; otherwise the whole wavefront
-// takes the general ones.  The branch is marked unlikely, so that what the
+// wavefront interchanges rows, but for the system's SWAP (every trip of the
+// Robertson workloads, 96 % of the HIRES ones at rtol 1e-6 and 81 % at 1e-4;
+// 83 % and 58 % without the SWAP), the factorisation and the solves without
+// the general interchanges and their fill serve, with the same values;
+// otherwise the whole wavefront takes the general ones, at three to five times
+// the instructions (HIRES, 2^17: the SWAP takes the record from 3.31 to 2.93
+// ms, the sweep from 6.39 to 5.61).  The branch is marked unlikely, so that what the
 // general path has no registers for moves inside it.
 template <class Sys, class Tab, class T, int NSC, bool ERR>
 __device__ __forceinline__ void ros_eval(const T* y, const T* p, T h, T* ynew, T* e) {
   constexpr int D = Sys::D;
   PlainMat<Sys, T> F;
-  if (__builtin_expect(!__any(ros_factor_plain<Sys, Tab, T>(y, p, h, F.w)), 1)) {
+  if (__builtin_expect(!__any(ros_factor_plain<Sys, Tab, T>(y, p, h, F)), 1)) {
     T u[Tab::S][D];
     int piv[D];
     ros_stages<Sys, Tab, T, PlainMat<Sys, T>, NSC>(y, p, h, F, piv, u, ynew);
@@ -560,7 +618,7 @@ __device__ __forceinline__ void ros_reverse(const T* yb, const T* p, T h, T* sU,
   constexpr int D = Sys::D;
   int piv[D];
   PlainMat<Sys, T> F;
-  if (__builtin_expect(!__any(ros_factor_plain<Sys, Tab, T>(yb, p, h, F.w)), 1)) {
+  if (__builtin_expect(!__any(ros_factor_plain<Sys, Tab, T>(yb, p, h, F)), 1)) {
     ros_reverse_of<Sys, Tab, T, U_LDS>(yb, p, h, F, piv, sU, cot, lin, g);
   } else {
     T W[D * D];

@@ -146,6 +146,8 @@ struct Hires {
   // nonzero pattern of the Jacobian (as jac below writes it), row i: bit j
   // where dF_i/dy_j is not identically zero
   static constexpr unsigned JAC_ROWS[8] = {0x07u, 0x03u, 0x1Cu, 0x0Eu, 0x70u, 0xF8u, 0xE0u, 0xE0u};
+  // the interchange that partial pivoting makes of I / (gamma h) - J at large h
+  static constexpr int SWAP[2] = {1, 3};
   template <class T>
   __device__ static inline void rhs(const T* y, const T* p, T* f) {
     f[0] = fmaT(p[2], y[2], fmaT(p[1], y[1], fmaT(-p[0], y[0], p[3])));
