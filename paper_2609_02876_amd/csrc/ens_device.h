@@ -93,6 +93,19 @@ __device__ __forceinline__ uint64_t wave_bump(unsigned long long* counter,
   return base + (uint64_t)rank_below(mask);
 }
 
+// max(|a|, |b|) in one instruction, of operands that are no signalling NaN
+// (fmax would canonicalise both first).  A NaN operand gives the other one.
+__device__ __forceinline__ double max_abs(double a, double b) {
+  double r;
+  asm("v_max_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+__device__ __forceinline__ float max_abs(float a, float b) {
+  float r;
+  asm("v_max_f32_e64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
+  return r;
+}
+
 // Sum over the 64 lanes of a wavefront, by butterfly exchanges: within quads
 // (DPP quad_perm, partners lane ^ 1 and lane ^ 2), within rows (DPP
 // row_half_mirror, then row_mirror: each exchanges a lane's half-row, then

@@ -276,19 +276,6 @@ __device__ __forceinline__ double mean_sq(const double* v, const double* sc) {
   return ss * (1.0 / (double)D);
 }
 
-// max(|a|, |b|) in one instruction, of operands that are no signalling NaN
-// (fmax would canonicalise both first).  A NaN operand gives the other one.
-__device__ __forceinline__ double max_abs(double a, double b) {
-  double r;
-  asm("v_max_f64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-__device__ __forceinline__ float max_abs(float a, float b) {
-  float r;
-  asm("v_max_f32_e64 %0, |%1|, |%2|" : "=v"(r) : "v"(a), "v"(b));
-  return r;
-}
-
 // Mean square of the error estimate e = h * esum against atol + rtol
 // max(|y|, |y_new|).
 template <class T, int D>
@@ -929,8 +916,10 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
       // a replay on a given mesh forms only the stages that enter y_new
       ros_eval<Sys, Tab, T, (MODE == MODE_FROZEN ? Tab::SU : Tab::S), MODE != MODE_FROZEN>(
           y, p, T(zero ? 1.0 : hh), ynew, e);
+      if (__any(zero)) {
 #pragma unroll
-      for (int c = 0; c < D; ++c) ynew[c] = zero ? y[c] : ynew[c];
+        for (int c = 0; c < D; ++c) ynew[c] = zero ? y[c] : ynew[c];
+      }
       if constexpr (MODE != MODE_FROZEN) err = ros_ms<D, T>(y, ynew, e, rtol, atol);
     } else {
       T kb[D];
