@@ -460,12 +460,13 @@ int launch_forward(const ens_problem* p, int mode, bool ckpt, const FwdArgs& fa,
 
 // Whether a record writes each taped step at once (DIRECT) or stages whole
 // lines.  At once up to 65,536 trajectories, one wavefront per SIMD (Lorenz /
-// Tsit5 on [0, 10], ms, staged then direct: 1,000: 0.45, 0.34; 32,768: 0.47,
-// 0.36; 65,536: 0.49, 0.39; 131,072: 0.75, 0.87; Robertson / Rodas4 65,536:
-// 0.34, 0.31), as long as the L2 holds each lane's open line.  Where the
+// Tsit5 on [0, 10], ms, staged then direct: 1,000: 0.41, 0.29; 32,768: 0.44,
+// 0.31; 65,536: 0.46, 0.34; 131,072: 0.70, 0.87; with a checkpoint every 64
+// steps 65,536: 0.44, 0.39; 131,072: 0.64, 0.75; Robertson / Rodas4 65,536:
+// 0.29, 0.26), as long as the L2 holds each lane's open line.  Where the
 // trajectories' tapes are a multiple of 16 KiB apart the open lines fall into
-// few of its sets: 32,768 still take 0.35, 65,536 take 0.48 at 16 KiB and
-// 0.54 at 32 KiB, so those are staged from 32,768 on.
+// few of its sets: 32,768 lose nothing, 65,536 a quarter of their time at 16
+// KiB and two fifths at 32 KiB, so those are staged from 32,768 on.
 bool direct_record(const FwdArgs& fa) {
   const int64_t stride = (int64_t)fa.rec.static_pages * fa.rec.page_bytes;
   return fa.ivp.n <= (stride % 16384 == 0 ? 32768 : 65536);

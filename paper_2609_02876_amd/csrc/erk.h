@@ -689,10 +689,10 @@ __device__ __forceinline__ void hermite_state(const T* y0, const T* y1, const T*
 // checkpointed tape's step size likewise, with no staging.  The stores wait
 // for nothing, so with one wavefront per SIMD, where the chain of a trial's
 // instructions is the time, the staging, the queue and the cooperative writes
-// are what it saves: 0.46 -> 0.34 ms for 1,000 Lorenz trajectories.  A store
+// are what it saves: 0.41 -> 0.29 ms for 1,000 Lorenz trajectories.  A store
 // instruction touches one line per lane, and the L2 has to hold every lane's
-// open line until it is whole: at 2^20 trajectories the same record takes
-// 7.9 ms, staged 4.6.
+// open line until it is whole: at 131,072 trajectories the same record takes
+// 0.87 ms, staged 0.70.
 template <class Sys, class Tab, class T, int MODE, bool CKPT, bool DEFER = false,
           bool DENSE = false, bool DIRECT = false>
 __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block) {
