@@ -1440,13 +1440,11 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   __shared__ uint4 s_h[CKPT ? H_GROUP / 2 * 256 : 1];
   const RecView& R = a.rec;
   const bool ok = valid && R.status[tr] == LANE_OK;
-  // CKPT: segments by index from the start of the mesh; the lane's last one
-  // and the wavefront's (every lane of the wavefront is here)
-  int F = -1, F_max = -1;
-  if constexpr (CKPT) {
-    if (ok && R.steps[tr] > 0) F = (R.steps[tr] - 1) / K;
-    F_max = wave_max(F);
-  }
+  // Segments (CKPT) or groups of TAPE_GROUP steps by index from the start of
+  // the mesh; the lane's last one and the wavefront's (every lane of the
+  // wavefront is here)
+  const int F = ok && R.steps[tr] > 0 ? (R.steps[tr] - 1) / (CKPT ? K : TAPE_GROUP) : -1;
+  const int F_max = __builtin_amdgcn_readfirstlane(wave_max(F));
   T* gpo = (T*)a.grad_p;
   T* gyo = (T*)a.grad_y0;
   T lam[D], gp[NP];
@@ -1619,15 +1617,18 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
     if constexpr (!AT_END) take_saves();  // the saves at the initial state
   } else {
     // Full tape, a group of TAPE_GROUP steps (for 32-byte records one line) at
-    // a time.  A lane's first group (the last of its tape) may be shorter; at
-    // the end of the inner loop it waits for the wavefront's others, so from
-    // then on all lanes fetch their groups in the same trips.
+    // a time, by the groups' index from the start of the mesh: lanes whose
+    // tape ends in an earlier group wait, and all lanes fetch and reverse
+    // their groups in the same trips.
     //
     // The next group is asked for when the last step of this one has been
     // read from LDS, and goes there without passing through registers, so it
     // travels while that step is reversed (through registers at the group's
     // first step: 2^20 Lorenz / Tsit5 4.16 ms, now 4.02; 1,000: 0.327, 0.308;
-    // 50,021 Robertson / Rosenbrock23: 0.623, 0.558).
+    // 50,021 Robertson / Rosenbrock23: 0.623, 0.558).  The shorter FP32 steps
+    // of a full chip do not cover it (2^18 Lorenz / Tsit5: 0.80 ms, asked for
+    // ahead 0.82; 100,003: 0.49 and 0.47), so those load through registers.
+    const bool ahead = sizeof(T) == 8 || n <= 131072;
     auto fetch = [&](const char* pgp, int g0) {
       if constexpr (STAGE) {
         // the reads of this lane's last group are done
@@ -1641,12 +1642,20 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
       }
     };
     const char* pgp = R.pages + (int64_t)page * R.page_bytes;
-    if (i > 0) fetch(pgp, slot & ~(TAPE_GROUP - 1));
-    while (i > 0) {
+    if (i > 0 && ahead) fetch(pgp, slot & ~(TAPE_GROUP - 1));
+    for (int f = F_max; f >= 0; --f) {
+      if (f > F) continue;
       const int g0 = slot & ~(TAPE_GROUP - 1);
       const char* rp = pgp + g0 * RB;
-      // the group is in LDS
-      if constexpr (STAGE) asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      if constexpr (STAGE) {
+        if (ahead) {
+          asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the group is in LDS
+        } else {
+          const uint4* src = reinterpret_cast<const uint4*>(__builtin_assume_aligned(rp, 16));
+#pragma unroll
+          for (int q = 0; q < TAPE_GROUP * CH; ++q) s_rd[q * 256 + threadIdx.x] = src[q];
+        }
+      }
       for (int j = slot & (TAPE_GROUP - 1); j >= 0; --j) {
         if constexpr (!AT_END) take_saves();
         RecBuf<T, D> b;
@@ -1665,7 +1674,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
               pgp = R.pages + (int64_t)page * R.page_bytes;
               slot = PAGE_STEPS - 1;
             }
-            fetch(pgp, slot & ~(TAPE_GROUP - 1));
+            if (ahead) fetch(pgp, slot & ~(TAPE_GROUP - 1));
           }
         }
         reverse_step(b.y, b.h);

@@ -65,9 +65,10 @@ constexpr unsigned jac_row_of(int, long) {
 struct SwapAt {
   int col, row;
 };
+// (built-in systems only: a registered one's members are its own)
 template <class S>
-constexpr auto swap_of(int) -> decltype(S::SWAP[0], SwapAt{}) {
-  return SwapAt{S::SWAP[0], S::SWAP[1]};
+constexpr auto swap_of(int) -> decltype(SwapAt{S::SWAP[0], S::SWAP[1]}) {
+  return S::ID < 1000 ? SwapAt{S::SWAP[0], S::SWAP[1]} : SwapAt{-1, -1};
 }
 template <class S>
 constexpr SwapAt swap_of(long) {
