@@ -1743,9 +1743,8 @@ __global__ void __launch_bounds__(256, (FwdBlocks<Sys, Tab, T>::value))
 
 // Full-tape record whose save states are formed afterwards by
 // erk_saves_kernel (explicit pairs), with wave-cooperative tape writes.  The
-// FP64 Lorenz / Tsit5 record needs 114 VGPRs at four blocks per CU; its 37 KB
-// of LDS (a whole group of records per lane and the write queue) admit no
-// more.  2^20 trajectories are 16 waves per SIMD: four full rounds.
+// FP64 Lorenz / Tsit5 record fits four blocks per CU; its 37 KB of LDS (a
+// whole group of records per lane and the write queue) admit no more.  2^20 trajectories are 16 waves per SIMD: four full rounds.
 template <class Sys, class Tab, class T>
 struct DeferBlocks {
   static constexpr int value =
@@ -1827,9 +1826,9 @@ __global__ void __launch_bounds__(256) dense_saves_kernel(const FwdArgs a) {
 }
 
 // Blocks per CU the compiler is asked to fit in the reverse sweep: 3 for the
-// FP64 Lorenz / Tsit5 sweep, which then lands at 124 registers with no
-// spill (4 waves per SIMD); asking for 4 gives the same occupancy with a
-// spill.  With a checkpointed tape it would land at 129, so 4.
+// FP64 Lorenz / Tsit5 sweep, which then lands at 116 registers with no
+// spill (4 waves per SIMD).  With a checkpointed tape it would land past 128,
+// so 4 (127, with 12 bytes of spill).
 // The built-in Rosenbrock systems of d < 6 as their records, short of a spill
 // in the path without interchanges (a reload waits behind the tape's loads).
 // No request for the others.

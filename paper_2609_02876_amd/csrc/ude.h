@@ -177,22 +177,24 @@ __device__ __forceinline__ float ude_join(float v) {
 // tanh in FP32 (relative error below 5e-7): for |x| < 0.55 the odd series
 // x + x^3 P(x^2), P of degree 4 fitted by least squares to (tanh(x)/x - 1)/x^2
 // on [0, 0.55]; above, 1 - 2 / (e^{2|x|} + 1) with the hardware exp2 and
-// reciprocal (the series avoids that form's cancellation near 0).
-__device__ __forceinline__ float ude_tanh_series(float x) {
+// reciprocal (the series avoids that form's cancellation near 0).  SERIES: |x|
+// is known to be below.
+template <bool SERIES = false>
+__device__ __forceinline__ float ude_tanh(float x) {
+  const float ax = fabsf(x);
+  float big = x;
+  if constexpr (!SERIES) {
+    const float e = __builtin_amdgcn_exp2f(ax * 2.8853900817779268f);  // 2^(2|x| / ln 2)
+    big = fmaT(-2.0f, __builtin_amdgcn_rcpf(e + 1.0f), 1.0f);
+  }
   const float x2 = x * x;
   float q = -0.026664944365620613f;
   q = fmaT(q, x2, 0.03440927714109421f);
   q = fmaT(q, x2, -0.05673672631382942f);
   q = fmaT(q, x2, 0.13355417549610138f);
   q = fmaT(q, x2, -0.3333379626274109f);
-  return fmaT(x * x2, q, x);
-}
-__device__ __forceinline__ float ude_tanh(float x) {
-  const float ax = fabsf(x);
-  const float e = __builtin_amdgcn_exp2f(ax * 2.8853900817779268f);  // 2^(2|x| / ln 2)
-  const float big = fmaT(-2.0f, __builtin_amdgcn_rcpf(e + 1.0f), 1.0f);
-  const float small = ude_tanh_series(x);
-  return ax < 0.55f ? small : copysignf(big, x);
+  const float small = fmaT(x * x2, q, x);
+  return SERIES || ax < 0.55f ? small : copysignf(big, x);
 }
 
 // tanh of a layer.  Where every |x| of the wavefront is below 0.55 (layers of
@@ -205,7 +207,7 @@ __device__ __forceinline__ void ude_tanh_layer(v16f& v) {
   for (int r = 0; r < 16; ++r) m = fmaxf(m, fabsf(v[r]));
   if (!__any(m >= 0.55f)) {
 #pragma unroll
-    for (int r = 0; r < 16; ++r) v[r] = ude_tanh_series(v[r]);
+    for (int r = 0; r < 16; ++r) v[r] = ude_tanh<true>(v[r]);
   } else {
 #pragma unroll
     for (int r = 0; r < 16; ++r) v[r] = ude_tanh(v[r]);
