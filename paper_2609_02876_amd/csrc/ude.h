@@ -119,7 +119,8 @@ struct UdeLds {
   float s_w1[2][2][16];  // [hf][k][r]: W1[U(r, hf)][k]
   float s_b3[2];
   float coef[6][6];      // Tsit5, [j][0]: b_j; [j][l], l > j: a_lj
-  alignas(16) float tile[UDE_WAVES][2][UDE_TILE];
+  // a wavefront's two tiles (delta2, h1); at the end its partial, along the row
+  alignas(16) float tile[UDE_WAVES][2 * UDE_TILE];
 
   // a compiler memory barrier before each use of the layers: without it the
   // loads leave the sweep's loop, and the registers they would stay in spill
@@ -325,8 +326,8 @@ struct LvUdeSweep {
 
     // stage delta2 and h1 as [trajectory][unit] tiles for the weight gradient
     // (registers 4 q .. 4 q + 3 hold four consecutive units)
-    float* td = const_cast<float*>(W.tile[wave][0]);
-    float* th = const_cast<float*>(W.tile[wave][1]);
+    float* td = const_cast<float*>(W.tile[wave]);
+    float* th = const_cast<float*>(W.tile[wave]) + UDE_TILE;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
       const int at = c * UDE_STRIDE + 8 * q + 4 * hf;
@@ -868,7 +869,7 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
   // this wavefront's partial of the weight gradient, in parameter order (its
   // tiles are free now), then the block's: the wavefronts' added in order
   const int l = __lane_id(), c = l & 31;
-  float* part = s_lds.tile[wave][0];
+  float* part = s_lds.tile[wave];
 #pragma unroll
   for (int r = 0; r < 16; ++r) part[UDE_OW2 + 32 * ude_unit(r, hf) + c] = g.w2[r];
 #pragma unroll
@@ -895,9 +896,9 @@ __global__ void __launch_bounds__(64 * UDE_WAVES, 2) ude_adjoint_kernel(const Ad
   __syncthreads();
   float* out = (float*)a.workspace + (int64_t)blockIdx.x * UDE_NP;
   for (int q = threadIdx.x; q < UDE_NP; q += 64 * UDE_WAVES) {
-    float v = s_lds.tile[0][0][q];
+    float v = s_lds.tile[0][q];
 #pragma unroll
-    for (int w = 1; w < UDE_WAVES; ++w) v = v + s_lds.tile[w][0][q];
+    for (int w = 1; w < UDE_WAVES; ++w) v = v + s_lds.tile[w][q];
     out[q] = v;
   }
 }
