@@ -225,21 +225,23 @@ __device__ __forceinline__ bool ros_factor_plain(const T* y, const T* p, T h,
 #pragma unroll
   for (int k = 0; k < D; ++k) {
     T best = fabs(W[k * D + k]);
-    if (k == SW.col) {
-      const T v = fabs(W[SW.row * D + k]);
-      F.sw = v > best;
-      best = pick(F.sw, v, best);
-      // the first of the largest is the pivot
+    if constexpr (SW.col >= 0) {
+      if (k == SW.col) {
+        const T v = fabs(W[SW.row * D + k]);
+        F.sw = v > best;
+        best = pick(F.sw, v, best);
+        // the first of the largest is the pivot
 #pragma unroll
-      for (int i = k + 1; i < D; ++i)
-        if (has(P.elim[k], i) && i != SW.row) {
-          const T o = fabs(W[i * D + k]);
-          other |= o > best || (i < SW.row && F.sw && o == best);
-        }
+        for (int i = k + 1; i < D; ++i)
+          if (has(P.elim[k], i) && i != SW.row) {
+            const T o = fabs(W[i * D + k]);
+            other |= o > best || (i < SW.row && F.sw && o == best);
+          }
 #pragma unroll
-      for (int j = 0; j < D; ++j)
-        if (has(P.before[k][k] | P.before[k][SW.row], j))
-          swap_where(F.sw, W[k * D + j], W[SW.row * D + j]);
+        for (int j = 0; j < D; ++j)
+          if (has(P.before[k][k] | P.before[k][SW.row], j))
+            swap_where(F.sw, W[k * D + j], W[SW.row * D + j]);
+      }
     }
     const T r = inverse(W[k * D + k]);
     W[k * D + k] = r;
