@@ -844,6 +844,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   bool side = false;
   int32_t S = 0, trials = 0;
   bool prev_rej = false;
+  RosTry rtry;
   // The tape.  A trajectory's reserved pages follow one another, so in them
   // the next place is found by adding: `tape` is where the next step goes
   // (CKPT: the current page), and only when the `room` steps (CKPT: pages)
@@ -915,7 +916,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
       T e[D];
       // a replay on a given mesh forms only the stages that enter y_new
       ros_eval<Sys, Tab, T, (MODE == MODE_FROZEN ? Tab::SU : Tab::S), MODE != MODE_FROZEN>(
-          y, p, T(zero ? 1.0 : hh), ynew, e);
+          y, p, T(zero ? 1.0 : hh), ynew, e, rtry);
       if (__any(zero)) {
 #pragma unroll
         for (int c = 0; c < D; ++c) ynew[c] = zero ? y[c] : ynew[c];
@@ -1548,6 +1549,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
     const int m = n - base < 256 ? (int)(n - base) : 256;
     uint4* scr = reinterpret_cast<uint4*>((char*)a.scratch + base * K * RB) +
                  ((int)threadIdx.x - (256 - m));
+    RosTry rtry;
     for (int f = F_max; f >= 0; --f) {
       const int len = f <= F ? slot + 1 : 0;
       T y[D];
@@ -1582,7 +1584,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
         if (j + 1 < len) {
           T ys[D];
           if constexpr (Tab::ROS) {
-            ros_eval<Sys, Tab, T, Tab::SU, false>(y, p, T(hh), ys, nullptr);
+            ros_eval<Sys, Tab, T, Tab::SU, false>(y, p, T(hh), ys, nullptr, rtry);
           } else {
             T k0[D], Y[SU][D], ylast[D], klast[D];
             Sys::rhs(y, p, k0);

@@ -449,6 +449,21 @@ __device__ __forceinline__ void ros_errvec(const T (&u)[Tab::S][D], T* e) {
   }
 }
 
+// Whether a wavefront tries the factorisation without interchanges.  A
+// registered system of d >= 6 that changes rows in step after step would pay
+// for it in vain each time (an 8 x 8 dense one in nearly every step, 16,384
+// trajectories, record / replay: always tried 4.51 / 4.15 ms, so 3.16 / 2.94,
+// always general 3.86 / 3.41); so after five failures in a row it is tried in
+// every ninth step only, until it succeeds.  With d <= 5 the vain attempt costs
+// less than the shorter general step gains (d = 5, the same way: 1.21 / 1.14
+// ms, always general 1.27 / 1.15), and for the built-in systems it hardly ever
+// fails, so those always try.  Either way gives the same values.
+struct RosTry {
+  static constexpr int FAILS = 5, WAIT = 8;
+  int failed = 0;  // in a row (the same in every lane of the wavefront)
+  int wait = 0;    // steps until the next attempt
+};
+
 // One step: y_new and, if ERR, the error estimate e.  Where no lane of the
 // wavefront interchanges rows, but for the system's SWAP (every trip of the
 // Robertson workloads, 96 % of the HIRES ones at rtol 1e-6 and 81 % at 1e-4;
@@ -459,20 +474,31 @@ __device__ __forceinline__ void ros_errvec(const T (&u)[Tab::S][D], T* e) {
 // ms, the sweep from 6.39 to 5.61).  The branch is marked unlikely, so that what the
 // general path has no registers for moves inside it.
 template <class Sys, class Tab, class T, int NSC, bool ERR>
-__device__ __forceinline__ void ros_eval(const T* y, const T* p, T h, T* ynew, T* e) {
+__device__ __forceinline__ void ros_eval(const T* y, const T* p, T h, T* ynew, T* e,
+                                         RosTry& rt) {
   constexpr int D = Sys::D;
-  PlainMat<Sys, T> F;
-  if (__builtin_expect(!__any(ros_factor_plain<Sys, Tab, T>(y, p, h, F)), 1)) {
-    T u[Tab::S][D];
-    int piv[D];
-    ros_stages<Sys, Tab, T, PlainMat<Sys, T>, NSC>(y, p, h, F, piv, u, ynew);
-    if constexpr (ERR) ros_errvec<Tab, D, T>(u, e);
+  constexpr bool ALWAYS = Sys::ID < 1000 || D < 6;
+  if (ALWAYS || __builtin_amdgcn_readfirstlane(rt.wait) == 0) {
+    PlainMat<Sys, T> F;
+    if (__builtin_expect(!__any(ros_factor_plain<Sys, Tab, T>(y, p, h, F)), 1)) {
+      T u[Tab::S][D];
+      int piv[D];
+      ros_stages<Sys, Tab, T, PlainMat<Sys, T>, NSC>(y, p, h, F, piv, u, ynew);
+      if constexpr (ERR) ros_errvec<Tab, D, T>(u, e);
+      if constexpr (!ALWAYS) rt.failed = 0;
+      return;
+    }
+    if constexpr (!ALWAYS) {
+      rt.failed = __builtin_amdgcn_readfirstlane(rt.failed) + 1;
+      rt.wait = rt.failed < RosTry::FAILS ? 0 : RosTry::WAIT;
+    }
   } else {
-    T W[D * D], u[Tab::S][D];
-    int piv[D];
-    ros_step<Sys, Tab, T, NSC>(y, p, h, W, piv, u, ynew);
-    if constexpr (ERR) ros_errvec<Tab, D, T>(u, e);
+    rt.wait = __builtin_amdgcn_readfirstlane(rt.wait) - 1;
   }
+  T W[D * D], u[Tab::S][D];
+  int piv[D];
+  ros_step<Sys, Tab, T, NSC>(y, p, h, W, piv, u, ynew);
+  if constexpr (ERR) ros_errvec<Tab, D, T>(u, e);
 }
 
 // The increments u_1..u_SU as the reverse reads them: a register array, or
