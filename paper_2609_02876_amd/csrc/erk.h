@@ -803,9 +803,12 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
       return r_tn;
   };
   if constexpr (MODE != MODE_SOLVE) R.first_page[tr] = -1;
+  // The next save and next_save * n, from which this lane's slots are found at
+  // each use: running pointers were moved about in every iteration, and the
+  // 64-bit product at each use cost the dense solve 1 to 7 % (a lane's saves
+  // are few, but some lane of the wavefront has one in most trips).
   int next_save = 0;
-  // This lane's slots of the next save are found from next_save at each use:
-  // saves are few, and running pointers were moved about in every iteration.
+  int64_t next_n = 0;
   // put_base: the base state of the next save, into the record's save_base.
   // The given-mesh modes on a full tape leave it to a kernel that copies the
   // states from the tape afterwards: their loops load a step size per step,
@@ -813,7 +816,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   auto put_base = [&](const T* yb, bool valid) {
     if constexpr (MODE == MODE_RECORD || (CKPT && MODE != MODE_SOLVE) ||
                   (DENSE && MODE != MODE_SOLVE)) {
-      T* sb = (T*)R.save_base + ((int64_t)next_save * D * n + tr);
+      T* sb = (T*)R.save_base + (next_n * D + tr);
 #pragma unroll
       for (int c = 0; c < D; ++c) sb[c * n] = valid ? yb[c] : T(NAN);
     }
@@ -821,26 +824,30 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   // dense output: the step's end state and its size, beside the base state
   auto put_dense = [&](const T* y1, double hstep) {
     if constexpr (DENSE && MODE != MODE_SOLVE) {
-      T* sb = (T*)R.save_base_hi + ((int64_t)next_save * D * n + tr);
+      T* sb = (T*)R.save_base_hi + (next_n * D + tr);
 #pragma unroll
       for (int c = 0; c < D; ++c) sb[c * n] = y1[c];
-      R.save_h[(int64_t)next_save * n + tr] = hstep;
+      R.save_h[next_n + tr] = hstep;
     }
   };
   // the next save's mesh index and offset
   auto put_point = [&](int32_t index, double offset) {
     if constexpr (MODE != MODE_SOLVE) {
-      const int64_t q = (int64_t)next_save * n + tr;
-      R.save_idx[q] = index;
-      R.save_dt[q] = offset;
+      R.save_idx[next_n + tr] = index;
+      R.save_dt[next_n + tr] = offset;
     }
   };
   auto put_state = [&](const T* yv, bool valid) {
-    T* ys = ysv + ((int64_t)next_save * D * n + tr);
+    T* ys = ysv + (next_n * D + tr);
 #pragma unroll
     for (int c = 0; c < D; ++c) ys[c * n] = valid ? yv[c] : T(NAN);
   };
   double ts = s_times[0];
+  auto advance = [&]() {
+    ++next_save;
+    next_n += n;
+    ts = s_times[next_save];
+  };
   bool side = false;
   int32_t S = 0, trials = 0;
   bool prev_rej = false;
@@ -948,8 +955,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
       put_state(ynew, true);
       put_base(y, true);
       put_point(S - 1, hh);
-      ++next_save;
-      ts = s_times[next_save];
+      advance();
       tnew = held_tn();
       side = ts < tnew;
       if (!side) {  // the last save of the interval: the new state held back
@@ -1045,8 +1051,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
           put_point(S - 1, ts - t);
           put_base(y, true);
           put_dense(ynew, hh);
-          ++next_save;
-          ts = s_times[next_save];
+          advance();
         }
       } else if constexpr (DENSE) {
         // the solve keeps nothing: saves inside this step take the step's
@@ -1066,8 +1071,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
           while (ts < tnew) {
             hermite_state<T, D>(y, ynew, f0, f1, hh, ts - t, yd);
             put_state(yd, true);
-            ++next_save;
-            ts = s_times[next_save];
+            advance();
           }
         }
       } else if constexpr (DEFER) {
@@ -1075,8 +1079,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
         while (ts < tnew) {
           put_point(S - 1, ts - t);
           put_base(y, true);
-          ++next_save;
-          ts = s_times[next_save];
+          advance();
         }
       } else if (ts < tnew) {
         side = true;
@@ -1137,7 +1140,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
 
   // saves at the last mesh point (t_s = t1): a side step of size zero
   const bool ok = (status == LANE_OK);
-  for (; next_save < ns; ++next_save) {
+  for (; next_save < ns; ++next_save, next_n += n) {
     put_state(y, ok);
     put_base(y, ok);
     put_dense(y, 0.0);
