@@ -783,9 +783,16 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   // In LDS because the lanes that hold no state back are most of them: in
   // registers the held values were moved about in every iteration.  (Wider
   // registered systems keep them in registers: their staged records fill the
-  // LDS.)
+  // LDS.)  Beside the staged step sizes of a checkpointed tape it leaves room
+  // for three blocks a CU instead of four.  The record is faster all the same
+  // (2^19 Lorenz / Tsit5 on [0, 3]: 0.82 ms, in registers 0.84; FP32 0.56,
+  // 0.59); the given-mesh modes, which wait for the mesh's step sizes, are not
+  // (FP32 Lorenz replay 0.68, in registers 0.64; 2^18 Robertson / Rosenbrock23
+  // replay 2.12, 2.01, refresh 2.27, 2.16), but for Rodas4, which then spills
+  // (refresh 0.84, in registers 0.94).
   constexpr int HELD = DEFER || DENSE ? 0 : (Tab::FSAL ? 2 : 1) * D;
-  constexpr bool HELD_LDS = HELD > 0 && D <= 8;
+  constexpr bool HELD_LDS = HELD > 0 && D <= 8 &&
+                            !(CKPT && MODE >= MODE_FROZEN && !(Tab::ROS && Tab::SU >= 6));
   __shared__ T s_held[HELD_LDS ? HELD * 256 : 1];
   __shared__ double s_tn[HELD_LDS ? 256 : 1];
   T r_held[HELD_LDS || HELD == 0 ? 1 : HELD];
