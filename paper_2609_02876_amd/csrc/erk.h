@@ -1501,9 +1501,6 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
   // Tape position of the step record of mesh step i (h_i, y_{i-1}).
   int32_t i = S;
   int slot = S > 0 ? (S - 1) % K : 0;
-  // Tape reads: the TAPE_GROUP records of a 128-byte line are loaded into
-  // LDS together (chunk-major, as in the record) when the sweep enters the
-  // line, so each line is fetched once although it serves TAPE_GROUP steps.
 
   // the saves based at mesh point i, from the last: their cotangents into lam
   auto take_saves = [&]() {
@@ -1513,15 +1510,10 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
       next_save();
     }
   };
-  // Where the loop takes them: on reaching a point, or at the end of the
-  // reverse step that reaches it (the six-stage Rodas4).  The same additions
-  // in the same order; only the register allocation differs, and measured
-  // in opposite directions: at the end, the HIRES Rodas4 sweep spills
-  // nothing instead of 92 B a lane and runs 4 % faster, while the FP64
-  // Lorenz / Tsit5 sweep needs 146 VGPRs instead of 124 and the HIRES
-  // Rosenbrock23 sweep runs 17 % slower.
-  constexpr bool AT_END = Tab::ROS && Tab::SU >= 6;
-  if constexpr (AT_END) take_saves();
+  // The loop takes them on reaching a point.  (At the end of the reverse step
+  // that reaches it, the same additions, the FP64 Lorenz / Tsit5 sweep needs 146
+  // registers instead of 116, 3 % slower at 2^20; the Rodas4 sweeps run alike,
+  // but for HIRES's checkpointed dense one, 3.65 ms against 3.32 at 2^15.)
 
   // Recompute the stages of mesh step i (size hh from yb) and reverse through
   // them: lam becomes the cotangent of mesh point i - 1.
@@ -1545,7 +1537,6 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
 #pragma unroll
     for (int c = 0; c < D; ++c) lam[c] = lin[c];
     --i;
-    if constexpr (AT_END) take_saves();
   };
 
   if constexpr (CKPT) {
@@ -1622,7 +1613,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
         RecBuf<T, D> b = ahead;
         if (j > 0 && j - 1 < len) fetch(j - 1);
         if (j < len) {
-          if constexpr (!AT_END) take_saves();
+          take_saves();
           reverse_step(b.y, b.h);
         }
       }
@@ -1631,7 +1622,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
         slot = K - 1;
       }
     }
-    if constexpr (!AT_END) take_saves();  // the saves at the initial state
+    take_saves();  // the saves at the initial state
   } else {
     // Full tape, a group of TAPE_GROUP steps (for 32-byte records one line) at
     // a time, by the groups' index from the start of the mesh: lanes whose
@@ -1674,7 +1665,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
         }
       }
       for (int j = slot & (TAPE_GROUP - 1); j >= 0; --j) {
-        if constexpr (!AT_END) take_saves();
+        take_saves();
         RecBuf<T, D> b;
         if constexpr (STAGE) {
           uint4* dst = reinterpret_cast<uint4*>(&b);
@@ -1697,7 +1688,7 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
         reverse_step(b.y, b.h);
       }
     }
-    if constexpr (!AT_END) take_saves();
+    take_saves();
   }
 
   if (a.loss_kind != LOSS_COTANGENT) loss = a.scale * loss;
