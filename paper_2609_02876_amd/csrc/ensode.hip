@@ -459,11 +459,16 @@ int launch_forward(const ens_problem* p, int mode, bool ckpt, const FwdArgs& fa,
 }
 
 // Whether a record writes each taped step at once (DIRECT) or stages whole
-// lines.  At once up to 65,536 trajectories, one wavefront per SIMD (Lorenz /
-// Tsit5 on [0, 10], ms, staged then direct: 1,000: 0.41, 0.29; 32,768: 0.44,
-// 0.31; 65,536: 0.46, 0.34; 131,072: 0.70, 0.87; with a checkpoint every 64
-// steps 65,536: 0.44, 0.39; 131,072: 0.64, 0.75; Robertson / Rodas4 65,536:
-// 0.29, 0.26), as long as the L2 holds each lane's open line.  Where the
+// lines.  At once up to 65,536 trajectories, one wavefront per SIMD, as long as
+// the L2 holds each lane's open line.  On [0, 10], ms, staged / direct:
+//                                    65,536     80,000    100,003    131,072
+//   Lorenz / Tsit5, rtol 1e-6      .48 / .35  .62 / .57  .64 / .65  .70 / .88
+//   with a checkpoint every 64     .40 / .36  .56 / .54  .56 / .60  .57 / .74
+//   FP32, rtol 1e-5                .31 / .31  .37 / .45  .38 / .52  .45 / .68
+//   Lorenz / Vern7, rtol 1e-8      .60 / .48  .81 / .69  .85 / .78  .91 / 1.00
+//   Robertson / Rodas4, [0, 1e5]   .28 / .27  .40 / .40  .43 / .45  .50 / .59
+// (1,000 Lorenz / Tsit5: .41 / .29).  The line is where none loses; the longer
+// FP64 steps would gain a little beyond it.  Where the
 // trajectories' tapes are a multiple of 16 KiB apart the open lines fall into
 // few of its sets: 32,768 lose nothing, 65,536 a quarter of their time at 16
 // KiB and two fifths at 32 KiB, so those are staged from 32,768 on.

@@ -784,12 +784,12 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   // registers the held values were moved about in every iteration.  (Wider
   // registered systems keep them in registers: their staged records fill the
   // LDS.)  Beside the staged step sizes of a checkpointed tape it leaves room
-  // for three blocks a CU instead of four.  The record is faster all the same
-  // (2^19 Lorenz / Tsit5 on [0, 3]: 0.82 ms, in registers 0.84; FP32 0.56,
-  // 0.59); the given-mesh modes, which wait for the mesh's step sizes, are not
-  // (FP32 Lorenz replay 0.68, in registers 0.64; 2^18 Robertson / Rosenbrock23
-  // replay 2.12, 2.01, refresh 2.27, 2.16), but for Rodas4, which then spills
-  // (refresh 0.84, in registers 0.94).
+  // for three blocks a CU instead of four.  The record is no slower for it
+  // (262,145 Lorenz / Tsit5 on [0, 10]: 1.15 ms, in registers 1.15; Robertson /
+  // Rosenbrock23 1.67, 1.72); the given-mesh modes, which wait for the mesh's
+  // step sizes, are (2^19 FP32 Lorenz replay 0.68, in registers 0.64; 2^18
+  // Robertson / Rosenbrock23 replay 2.12, 2.01, refresh 2.27, 2.16), but for
+  // Rodas4, which then spills (refresh 0.84, in registers 0.94).
   constexpr int HELD = DEFER || DENSE ? 0 : (Tab::FSAL ? 2 : 1) * D;
   constexpr bool HELD_LDS = HELD > 0 && D <= 8 &&
                             !(CKPT && MODE >= MODE_FROZEN && !(Tab::ROS && Tab::SU >= 6));
@@ -1634,8 +1634,9 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
     // travels while that step is reversed (through registers at the group's
     // first step: 2^20 Lorenz / Tsit5 4.16 ms, now 4.02; 1,000: 0.327, 0.308;
     // 50,021 Robertson / Rosenbrock23: 0.623, 0.558).  The shorter FP32 steps
-    // of a full chip do not cover it (2^18 Lorenz / Tsit5: 0.80 ms, asked for
-    // ahead 0.82; 100,003: 0.49 and 0.47), so those load through registers.
+    // of a full chip do not cover it, so those load through registers (FP32
+    // Lorenz / Tsit5 through registers / ahead, ms: 100,003 .338 / .319, 131,072
+    // .362 / .334, 200,000 .519 / .552, 2^18 .80 / .82).
     const bool ahead = sizeof(T) == 8 || n <= 131072;
     auto fetch = [&](const char* pgp, int g0) {
       if constexpr (STAGE) {
@@ -1733,7 +1734,9 @@ __device__ __forceinline__ void erk_adjoint_body(const AdjArgs& a, int64_t block
 // systems of d < 6 (4: what the path without interchanges needs; the general
 // one, which they hardly take, spills a little).  No request otherwise: at two
 // waves per SIMD HIRES's path without interchanges runs 10 % faster, but the
-// general one spills some 640 B a lane and takes eight times as long.
+// general one spills some 640 B a lane and takes eight times as long.  (The
+// records of checkpointed tapes have LDS for three blocks; what they are asked
+// for then only bounds their registers.)
 template <class Sys, class Tab, class T>
 struct FwdBlocks {
   static constexpr int value =
