@@ -709,6 +709,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   // save times in LDS (lane-varying index, short latency); slot n_save holds
   // +inf so that "no save left" needs no branch
   __shared__ double s_times[65];
+  __shared__ int64_t s_slot[DEFER ? 65 : 1];  // s_slot[s] = s n
   // Tape staging.  COOP (full-tape records of the explicit pairs): every
   // record of a group waits here, and the wavefront writes the completed
   // groups together (flush_groups_wave).  Otherwise each lane collects the
@@ -730,6 +731,9 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   if (threadIdx.x < 65)
     s_times[threadIdx.x] = (int)threadIdx.x < a.ivp.n_save ? save_time_at(a.ivp.st, threadIdx.x)
                                                           : INFINITY;
+  if constexpr (DEFER) {
+    if (threadIdx.x < 65) s_slot[threadIdx.x] = (int64_t)threadIdx.x * n;
+  }
   __syncthreads();
   if (tr >= n) return;
   const double t0 = a.ivp.t0, t1 = a.ivp.t1;
@@ -810,12 +814,20 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
       return r_tn;
   };
   if constexpr (MODE != MODE_SOLVE) R.first_page[tr] = -1;
-  // The next save and next_save * n, from which this lane's slots are found at
-  // each use: running pointers were moved about in every iteration, and the
-  // 64-bit product at each use cost the dense solve 1 to 7 % (a lane's saves
-  // are few, but some lane of the wavefront has one in most trips).
+  // The next save, and next_save * n, from which this lane's slots are found at
+  // each use: carried and added to (running pointers to the slots were moved
+  // about in every iteration; the 64-bit product at each use cost the dense
+  // solve 2 to 5 %, for a lane's saves are few, but some lane of the wavefront has
+  // one in most trips), or, in the deferred records, read from a table in LDS
+  // (carried it cost the record of 8 Lorenz / Tsit5 trajectories 2 %).
   int next_save = 0;
   int64_t next_n = 0;
+  auto slot_n = [&]() -> int64_t {
+    if constexpr (DEFER)
+      return s_slot[next_save];
+    else
+      return next_n;
+  };
   // put_base: the base state of the next save, into the record's save_base.
   // The given-mesh modes on a full tape leave it to a kernel that copies the
   // states from the tape afterwards: their loops load a step size per step,
@@ -823,7 +835,7 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   auto put_base = [&](const T* yb, bool valid) {
     if constexpr (MODE == MODE_RECORD || (CKPT && MODE != MODE_SOLVE) ||
                   (DENSE && MODE != MODE_SOLVE)) {
-      T* sb = (T*)R.save_base + (next_n * D + tr);
+      T* sb = (T*)R.save_base + (slot_n() * D + tr);
 #pragma unroll
       for (int c = 0; c < D; ++c) sb[c * n] = valid ? yb[c] : T(NAN);
     }
@@ -831,28 +843,29 @@ __device__ __forceinline__ void erk_forward_body(const FwdArgs& a, int64_t block
   // dense output: the step's end state and its size, beside the base state
   auto put_dense = [&](const T* y1, double hstep) {
     if constexpr (DENSE && MODE != MODE_SOLVE) {
-      T* sb = (T*)R.save_base_hi + (next_n * D + tr);
+      T* sb = (T*)R.save_base_hi + (slot_n() * D + tr);
 #pragma unroll
       for (int c = 0; c < D; ++c) sb[c * n] = y1[c];
-      R.save_h[next_n + tr] = hstep;
+      R.save_h[slot_n() + tr] = hstep;
     }
   };
   // the next save's mesh index and offset
   auto put_point = [&](int32_t index, double offset) {
     if constexpr (MODE != MODE_SOLVE) {
-      R.save_idx[next_n + tr] = index;
-      R.save_dt[next_n + tr] = offset;
+      const int64_t q = slot_n() + tr;
+      R.save_idx[q] = index;
+      R.save_dt[q] = offset;
     }
   };
   auto put_state = [&](const T* yv, bool valid) {
-    T* ys = ysv + (next_n * D + tr);
+    T* ys = ysv + (slot_n() * D + tr);
 #pragma unroll
     for (int c = 0; c < D; ++c) ys[c * n] = valid ? yv[c] : T(NAN);
   };
   double ts = s_times[0];
   auto advance = [&]() {
     ++next_save;
-    next_n += n;
+    if constexpr (!DEFER) next_n += n;
     ts = s_times[next_save];
   };
   bool side = false;
